@@ -416,6 +416,7 @@ __device__ __forceinline__ void colpass_tiles(const ColPassArgs &A, int64_t t0, 
       }
     }
     if constexpr (ONE) break;
+    __syncthreads();  // the next tile is staged in the first layout, which may not be the one read last
   }
 }
 

@@ -87,13 +87,35 @@ __device__ __forceinline__ void wht_regs(T (&re)[R], T (&im)[R]) {
   }
 }
 
-// Move the tile from layout SA to layout SB through LDS (all NT threads must call it).
-// Threads with act == false (padding threads of a block larger than the tile) skip the LDS traffic.
+// Moving a tile from layout SA to layout SB through LDS.  In a layout with S <= 6 the thread bits
+// above the lane (tau >> 6) are the top bits of the tile index, so a wave holds the contiguous index
+// range [w 2^(6+RB), (w+1) 2^(6+RB)), which is also its own stretch of the LDS buffer:
+//   * SA <= 6 and SB <= 6: the values never leave the wave.  LDS instructions of one wave execute in
+//     order, so no workgroup barrier is needed, only that the compiler keeps the order (wave_order).
+//   * otherwise a barrier separates the writes from the reads.  One before the writes is needed only
+//     when they go to other waves' stretches (SA > 6): consecutive moves chain (the layout read last is
+//     the layout written next), so for SA <= 6 every wave last read its own stretch.
+// Without the barriers the waves of a workgroup drift apart and one wave's LDS traffic overlaps
+// another's butterflies (barriers per FP32 row tile of 2^15 values: 8 -> 4, of 2^11 values: 8 -> 0).
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__host__ __device__ constexpr bool in_wave(int SA, int SB) { return SA <= 6 && SB <= 6; }
+template <bool BARRIER>
+__device__ __forceinline__ void lds_order() {
+  if constexpr (BARRIER) __syncthreads();
+  else wave_order();
+}
+
+// All NT threads must call it.  Threads with act == false (padding threads of a block larger than the
+// tile) skip the LDS traffic.
 template <typename T, int R, int RB, int SA, int SB>
 __device__ __forceinline__ void relayout(T (&re)[R], T (&im)[R], vec2<T> *lds, uint32_t tau, bool act = true) {
   const uint32_t ba = ldspad<RB>(lay_base<SA, RB>(tau));
   const uint32_t bb = ldspad<RB>(lay_base<SB, RB>(tau));
-  __syncthreads();  // earlier readers of lds are done
+  lds_order<(SA > 6)>();  // earlier readers of the written stretch are done
   if (act) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -103,7 +125,7 @@ __device__ __forceinline__ void relayout(T (&re)[R], T (&im)[R], vec2<T> *lds, u
       lds[ba + ldspad<RB>(lay_off<SA, RB>(r))] = v;
     }
   }
-  __syncthreads();
+  lds_order<!in_wave(SA, SB)>();
   if (act) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -115,24 +137,23 @@ __device__ __forceinline__ void relayout(T (&re)[R], T (&im)[R], vec2<T> *lds, u
 }
 
 // Same as relayout, for tiles too large to stage both components at once: the real parts, then the
-// imaginary parts, go through a scalar LDS buffer of 2^TB (+ padding) values.
-// Same as relayout, for tiles too large to stage both components at once: the real parts, then the
-// imaginary parts, go through a scalar LDS buffer of 2^TB (+ padding) values.
-template <typename T, int R, int RB, int SA, int SB>
+// imaginary parts, go through a scalar LDS buffer of 2^TB (+ padding) values.  SECOND: the buffer was
+// just read in layout SB (the other component), possibly by other waves.
+template <typename T, int R, int RB, int SA, int SB, bool SECOND>
 __device__ __forceinline__ void relayout_one(T (&v)[R], T *lds, uint32_t tau) {
   const uint32_t ba = ldspad<RB>(lay_base<SA, RB>(tau));
   const uint32_t bb = ldspad<RB>(lay_base<SB, RB>(tau));
-  __syncthreads();
+  lds_order<(SECOND ? !in_wave(SA, SB) : SA > 6)>();
 #pragma unroll
   for (int r = 0; r < R; ++r) lds[ba + ldspad<RB>(lay_off<SA, RB>(r))] = v[r];
-  __syncthreads();
+  lds_order<!in_wave(SA, SB)>();
 #pragma unroll
   for (int r = 0; r < R; ++r) v[r] = lds[bb + ldspad<RB>(lay_off<SB, RB>(r))];
 }
 template <typename T, int R, int RB, int SA, int SB>
 __device__ __forceinline__ void relayout_split(T (&re)[R], T (&im)[R], T *lds, uint32_t tau) {
-  relayout_one<T, R, RB, SA, SB>(re, lds, tau);
-  relayout_one<T, R, RB, SA, SB>(im, lds, tau);
+  relayout_one<T, R, RB, SA, SB, false>(re, lds, tau);
+  relayout_one<T, R, RB, SA, SB, true>(im, lds, tau);
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs (workgroup b runs on XCD b mod 8).  This
