@@ -30,19 +30,6 @@ __host__ __device__ constexpr int pow3floor(int x) { return x < 3 ? 1 : 3 * pow3
 // log3 of a power of 3
 __host__ __device__ constexpr int log3c(int x) { return x < 3 ? 0 : 1 + log3c(x / 3); }
 
-// Raw buffer view of n_bytes of global memory (gfx9 buffer descriptor: no stride, no format
-// conversion).  Loads through it take a per-lane byte offset and a uniform byte offset (an SGPR), so
-// an address that is a per-thread part plus a wave-uniform part costs no vector instruction; an
-// offset past n_bytes reads zero.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_view(const void *p, uint32_t n_bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)n_bytes, 0x00020000);
-}
-__device__ __forceinline__ float2 buf_ld(float2 *, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0));
-}
-__device__ __forceinline__ double2 buf_ld(double2 *, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
-}
 // rows per row-pass tile: a power of 3 when rows are parts of a shift pair (WRITE), else as many
 // whole rows (shift pairs) as the block holds
 __host__ __device__ constexpr int mana_rows_per_tile(int NT, int TPR, bool write) {

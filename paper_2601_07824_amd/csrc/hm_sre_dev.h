@@ -22,6 +22,13 @@ __device__ __forceinline__ void cmul_conj(vec2<T> y, vec2<T> x, T &re, T &im) {
 // r at row position tlo + (r << S0)) form the folded vector u of shift a (see the file comment).
 // CH bounds how many registers' loads may be in flight: a scheduling fence after every CH values
 // keeps the compiler from hoisting all 2R gathers (register pressure decides occupancy).
+//
+// Row-tasks of whole waves (S0 >= 6; a, ch and the state the same for all lanes of a wave): the element
+// index of every gather is a per-lane part (row and thread bits, the same for all registers) plus a
+// part that depends on the register and the shift only.  The loads take the first as their lane offset
+// and the second as their scalar offset, so the 2R addresses cost no vector instruction (as global loads
+// two each, 4 of about 46 per folded value).  Shorter rows (several per wave) measured slower that way
+// (rows of 2^9 in the two-pass row pass: 56 -> 61 us per 2^25 values) and keep the global loads.
 template <typename T, int RB, int NL, int CH = (1 << RB)>
 __device__ __forceinline__ void sre_product(const vec2<T> *__restrict__ psi, uint32_t half, uint64_t a, uint64_t ch,
                                             uint32_t tlo, bool active, T (&re)[1 << RB], T (&im)[1 << RB]) {
@@ -46,6 +53,41 @@ __device__ __forceinline__ void sre_product(const vec2<T> *__restrict__ psi, uin
       if constexpr (CH < R) {
         if ((r + 1) % CH == 0) __builtin_amdgcn_sched_barrier(0);
       }
+    }
+  } else if constexpr (S0 >= 6) {
+    // Fold bit j is inserted into the row index (j >= NL), the register bits (S0 <= j < NL: register
+    // part ins0(r, j - S0)) or the thread bits (j < S0: the register bits move up by one, ins0(r, 0) = 2r).
+    constexpr uint32_t VB = sizeof(vec2<T>);
+    const uint32_t a32 = (uint32_t)a;  // below 2^26
+    const int j = 31 - __builtin_clz(a32);
+    const uint32_t xr = j >= NL ? ins0_32((uint32_t)ch, j - NL) : (uint32_t)ch << 1;
+    const uint32_t yr = j >= NL ? xr ^ (a32 >> NL) : xr;
+    const uint32_t xt = j >= S0 ? tlo : ins0_32(tlo, j);
+    const uint32_t yt = xt ^ (a32 & (uint32_t)(SEG - 1));
+    const int jj = j < S0 ? 0 : j >= NL ? RB : j - S0;
+    const uint32_t lomask = (1u << jj) - 1u, amid = (a32 >> S0) & (uint32_t)(R - 1);
+    const uint32_t vx = ((xr << NL) + xt) * VB, vy = ((yr << NL) + yt) * VB;
+    const __amdgpu_buffer_rsrc_t rs = buf_view(uniform_ptr(psi), half * 2u * VB);
+    // two groups of G registers in flight: group g + 1 is requested before the products wait for group g
+    constexpr int G = R < 4 ? R : 4, NG = R / G;
+    vec2<T> px[2][G], py[2][G];
+    auto request = [&](int g) {
+#pragma unroll
+      for (int i = 0; i < G; ++i) {
+        const uint32_t r = (uint32_t)(g * G + i);
+        const uint32_t e = 2u * r - (r & lomask);  // ins0(r, jj)
+        px[g & 1][i] = buf_ld((vec2<T> *)nullptr, rs, vx, (e << S0) * VB);
+        py[g & 1][i] = buf_ld((vec2<T> *)nullptr, rs, vy, ((e ^ amid) << S0) * VB);
+      }
+    };
+    request(0);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      if (g + 1 < NG) request(g + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < G; ++i) cmul_conj<T>(py[g & 1][i], px[g & 1][i], re[g * G + i], im[g * G + i]);
+      __builtin_amdgcn_sched_barrier(0);
     }
   } else {
     const int j = 63 - __builtin_clzll(a);

@@ -56,6 +56,16 @@ struct RowPassArgs {
   const void *psis[HM_BATCH_PTRS];
 };
 
+// Index bits of a row that are transformed across the lanes (wht_lanes) instead of in a last round of
+// their own: one or two left-over bits of FP64 tiles, where the round's re-layout moves 32 B of LDS
+// traffic per value (measured: 2^14 values 128 -> 113, 2^13 values 85 -> 75 clocks per 64 values and CU).
+// FP32 tiles gain nothing (their row pass waits on the gathers, not on LDS).
+template <typename T>
+__host__ __device__ constexpr int row_lane_bits(int NL, int RB, bool write) {
+  const int left = RB == 0 ? 0 : NL - (NL - 1) / RB * RB;  // bits of the last round
+  return sizeof(T) == 8 && RB == 4 && !write && NL > RB && left <= 2 ? left : 0;
+}
+
 // Row-pass tile shape and LDS needs (shared by the stand-alone and the pipelined kernels).
 template <typename T, int NT, int RB, int NL, bool SPLIT>
 struct RowShape {
@@ -102,7 +112,8 @@ __device__ __forceinline__ void rowpass_tiles(const Args &A, int64_t t0, int64_t
   constexpr int TB = LT + RB;
   static_assert(TB >= NL && NL >= RB, "tile must hold whole rows");
   constexpr int S0 = NL - RB;
-  constexpr int K = RB == 0 ? 0 : (NL + RB - 1) / RB;
+  constexpr int LB = row_lane_bits<T>(NL, RB, WRITE);
+  constexpr int K = RB == 0 ? 0 : (NL + RB - 1) / RB - (LB > 0 ? 1 : 0);
   static_assert(K <= 4, "at most four rounds");
   constexpr int SEG = 1 << S0;           // threads per row-task
   constexpr int G = 1 << (TB - NL);      // row-tasks per tile
@@ -110,7 +121,7 @@ __device__ __forceinline__ void rowpass_tiles(const Args &A, int64_t t0, int64_t
 
   const vec2<T> *__restrict__ psi = (const vec2<T> *)A.psi;
   const uint32_t tlo = tau & (SEG - 1);
-  const uint32_t g = tau >> S0;
+  const uint32_t g = WAVE_UNIFORM ? __builtin_amdgcn_readfirstlane(tau >> S0) : tau >> S0;
   const uint32_t half = 1u << A.nf;
 
   for (int64_t tile = t0; tile < A.n_tiles; tile += tstep) {
@@ -142,7 +153,8 @@ __device__ __forceinline__ void rowpass_tiles(const Args &A, int64_t t0, int64_t
     T re[R], im[R];
     sre_product<T, RB, NL, (SPLIT || WRITE) ? 8 : R>(ps, half, a, ch, tlo, active, re, im);
 
-    // NL butterfly stages: K rounds, round k holds tile bits [S_k, S_k + RB) in registers.
+    // NL butterfly stages: K rounds, round k holds tile bits [S_k, S_k + RB) in registers; then the
+    // lane stages.
     if constexpr (K >= 1) wht_regs<T, R, 0, rp_H(NL, RB, 0)>(re, im);
     if constexpr (K >= 2) {
       if constexpr (SPLIT) relayout_split<T, R, RB, rp_S(NL, RB, 0), rp_S(NL, RB, 1)>(re, im, lds, tau);
@@ -159,6 +171,7 @@ __device__ __forceinline__ void rowpass_tiles(const Args &A, int64_t t0, int64_t
       else relayout<T, R, RB, rp_S(NL, RB, 2), rp_S(NL, RB, 3)>(re, im, lds, tau);
       wht_regs<T, R, 0, rp_H(NL, RB, 3)>(re, im);
     }
+    if constexpr (LB > 0) wht_lanes<T, R, LB>(re, im, tau);
 
     if constexpr (WRITE) {
       // Final layout has S = 0: register r holds row position b = r | (tlo << RB).  It is stored at

@@ -38,6 +38,28 @@ __device__ __forceinline__ void st32(V *base, uint32_t idx, V v) {
   *reinterpret_cast<V *>(reinterpret_cast<char *>(base) + (uint32_t)(idx * (uint32_t)sizeof(V))) = v;
 }
 
+// Raw buffer view of n_bytes of global memory (gfx9 buffer descriptor: no stride, no format
+// conversion).  Loads through it take a per-lane byte offset and a uniform byte offset (an SGPR), so
+// an address that is a per-thread part plus a wave-uniform part costs no vector instruction; an
+// offset past n_bytes reads zero.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_view(const void *p, uint32_t n_bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)n_bytes, 0x00020000);
+}
+__device__ __forceinline__ float2 buf_ld(float2 *, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0));
+}
+__device__ __forceinline__ double2 buf_ld(double2 *, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
+}
+// A pointer that is the same in every lane, in scalar registers (a buffer view of one held in vector
+// registers would be looped over its distinct values).
+template <typename V>
+__device__ __forceinline__ const V *uniform_ptr(const V *p) {
+  const uint64_t u = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+  return (const V *)(((uint64_t)hi << 32) | lo);
+}
+
 template <int S, int RB>
 __device__ __forceinline__ uint32_t lay(uint32_t tau, uint32_t rho) {
   return (tau & ((1u << S) - 1u)) | (rho << S) | ((tau >> S) << (S + RB));
@@ -85,6 +107,36 @@ __device__ __forceinline__ void wht_regs(T (&re)[R], T (&im)[R]) {
       }
     }
   }
+}
+
+// Walsh-Hadamard stages on the KB <= 2 lowest tile-index bits where they sit in the lowest lane bits,
+// without LDS: x + s p with p the partner's value (one DPP quad permutation per word) and s = +1 / -1 by
+// the lane's bit, the same rounding as a butterfly.  The lanes with s = -1 hold the negative of the
+// transform, a sign that depends on the index only: sums of |x|^2q and stages along other bits do not
+// see it.
+template <int CTRL>
+__device__ __forceinline__ float lane_move(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double lane_move(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <typename T, int R, int CTRL>
+__device__ __forceinline__ void lane_stage(T (&re)[R], T (&im)[R], T s) {
+#pragma unroll
+  for (int r = 0; r < R; ++r) re[r] = fmaT(lane_move<CTRL>(re[r]), s, re[r]);
+#pragma unroll
+  for (int r = 0; r < R; ++r) im[r] = fmaT(lane_move<CTRL>(im[r]), s, im[r]);
+}
+template <typename T, int R, int KB>
+__device__ __forceinline__ void wht_lanes(T (&re)[R], T (&im)[R], uint32_t tau) {
+  static_assert(KB <= 2, "quad permutations");
+  if constexpr (KB >= 1) lane_stage<T, R, 0xB1>(re, im, (tau & 1u) ? T(-1) : T(1));  // quad_perm 1,0,3,2
+  if constexpr (KB >= 2) lane_stage<T, R, 0x4E>(re, im, (tau & 2u) ? T(-1) : T(1));  // quad_perm 2,3,0,1
 }
 
 // Moving a tile from layout SA to layout SB through LDS.  In a layout with S <= 6 the thread bits
