@@ -99,15 +99,38 @@ __global__ __launch_bounds__((1 << (NL - RB)) < 64 ? 64 : (1 << (NL - RB))) void
     // sums and the adjoint seed w
     const T kf = (a == 0) ? T(1) : T(2);
     T l1 = T(0), lq = T(0);
+    if (Q2) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const T tr = re[r] * re[r], ti = im[r] * im[r];
-      l1 += tr + ti;
-      if (Q2) lq = fmaT(tr, tr, fmaT(ti, ti, lq));
-      else lq += (tr > T(0) ? (T)pow(tr, (T)A.q) : T(0)) + (ti > T(0) ? (T)pow(ti, (T)A.q) : T(0));
-      re[r] = wfold<T, Q2>(re[r], kf, A.q);
-      im[r] = wfold<T, Q2>(im[r], kf, A.q);
+      for (int r = 0; r < R; ++r) {
+        const T tr = re[r] * re[r], ti = im[r] * im[r];
+        l1 += tr + ti;
+        lq = fmaT(tr, tr, fmaT(ti, ti, lq));
+      }
+    } else if (sizeof(T) == 8 && A.q == 3.0) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const T tr = re[r] * re[r], ti = im[r] * im[r];
+        l1 += tr + ti;
+        lq += tr * tr * tr + ti * ti * ti;
+      }
+    } else {
+      // FP32 q = 3 stays with pow too: it rounds t^3 once, and the cube of the identity's value carries a
+      // good part of S_3
+      T h = T(0);  // t of the real part, kept for its imaginary part
+      bool second = false;
+      T pr = T(0);
+      each_real_rotating<T, R, (R < 2 ? R : 2), 1>(re, im, [&](T x) {
+        const T t = x * x, p = t > T(0) ? (T)pow(t, (T)A.q) : T(0);
+        if (second) {
+          l1 += h + t;
+          lq += pr + p;
+        }
+        h = t;
+        pr = p;
+        second = !second;
+      });
     }
+    adjoint_seeds<T, R, Q2>(re, im, kf, A.q);
     if (tact) {
       const double f = (a == 0) ? 1.0 : 4.0;
       s1 += f * (double)l1;

@@ -146,12 +146,24 @@ __device__ __forceinline__ void sre_product(const vec2<T> *__restrict__ psi, uin
 
 }
 
-// Adjoint seed of one folded real value: |k x|^{2q-2} x (k = 2 for a != 0, 1 for a = 0).
-template <typename T, bool Q2>
-__device__ __forceinline__ T wfold(T x, T k, double q) {
-  if (Q2) return (k * k) * (x * x) * x;
-  const T ax = fabs(k * x);
-  return ax > T(0) ? (T)pow(ax, (T)(2.0 * q - 2.0)) * x : T(0);
+// Adjoint seeds: every real value x becomes |k x|^{2q-2} x (k = 2 for a != 0, 1 for a = 0).  q = 3 has a form
+// of its own (with pow for every value the gradient of M_3 took three times that of M_2); other q call
+// pow, two registers per pass of a rotating loop.
+template <typename T, int R, bool Q2>
+__device__ __forceinline__ void adjoint_seeds(T (&re)[R], T (&im)[R], T k, double q) {
+  if (Q2) {
+    each_real(re, im, [&](T &x) { x = (k * k) * (x * x) * x; });
+  } else if (q == 3.0) {
+    each_real(re, im, [&](T &x) {
+      const T t = (k * k) * (x * x);
+      x = t * t * x;
+    });
+  } else {
+    each_real_rotating<T, R, (R < 2 ? R : 2), 1>(re, im, [&](T &x) {
+      const T ax = fabs(k * x);
+      x = ax > T(0) ? (T)pow(ax, (T)(2.0 * q - 2.0)) * x : T(0);
+    });
+  }
 }
 
 }  // namespace hm

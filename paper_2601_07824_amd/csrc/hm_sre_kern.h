@@ -205,21 +205,12 @@ __device__ __forceinline__ void rowpass_tiles(const Args &A, int64_t t0, int64_t
         }
       }
     } else {
-      Acc<T, QM> acc;
-      acc.zero();
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        acc.add(re[r], A.qa);
-        acc.add(im[r], A.qa);
-      }
-      double s[Acc<T, QM>::N];
-#pragma unroll
-      for (int k = 0; k < Acc<T, QM>::N; ++k) s[k] = seg_sum<NT, SEG>((double)acc.a[k], red, tau);
-      if (active && tlo == 0) {
-        unfold_scale(s, A.nacc, A.qa, a == 0);
-        double *o = A.shift_sums + slot * A.nacc;
-        for (int k = 0; k < A.nacc; ++k) o[k] = bad ? __builtin_nan("") : s[k];
-      }
+      double *o = A.shift_sums + slot * A.nacc;
+      double s0 = 0.0;
+      tile_sums<T, R, NT, SEG, QM>(re, im, A.qa, red, tau, [&](int k, double s) {
+        if (k == 0) s0 = s;
+        if (active && tlo == 0) o[k] = bad ? __builtin_nan("") : unfold_sum(k, s, s0, A.qa, a == 0);
+      });
     }
     if constexpr (ONE) break;
   }
@@ -377,27 +368,13 @@ __device__ __forceinline__ void colpass_tiles(const ColPassArgs &A, int64_t t0, 
       else relayout<T, R, RB, cp_S(NH, RB, CB, 2), cp_S(NH, RB, CB, 3)>(re, im, lds, tau);
       wht_regs<T, R, cp_L(NH, RB, CB, 3), cp_H(NH, RB, CB, 3)>(re, im);
     }
-    Acc<T, QM> acc;
-    acc.zero();
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      acc.add(re[r], A.qa);
-      acc.add(im[r], A.qa);
-    }
-    double s[Acc<T, QM>::N];
-#pragma unroll
-    for (int k = 0; k < Acc<T, QM>::N; ++k) s[k] = seg_sum<NT, NT>((double)acc.a[k], red, tau);
-    if (tau == 0) {
-      double *o = A.partials + (slot * A.n_cb + cb) * A.nacc;
-      for (int k = 0; k < A.nacc; ++k) o[k] = s[k];
-    }
+    double *o = A.partials + (slot * A.n_cb + cb) * A.nacc;
+    tile_sums<T, R, NT, NT, QM>(re, im, A.qa, red, tau, [&](int k, double s) {
+      if (tau == 0) o[k] = s;
+    });
     if constexpr (ADJ) {
       const T kf = (A.a0 + (uint64_t)slot == 0) ? T(1) : T(2);
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        re[r] = wfold<T, QM == 2>(re[r], kf, A.qa.q[0]);
-        im[r] = wfold<T, QM == 2>(im[r], kf, A.qa.q[0]);
-      }
+      adjoint_seeds<T, R, QM == 2>(re, im, kf, A.qa.q[0]);
       if constexpr (K >= 4) {
         wht_regs<T, R, cp_L(NH, RB, CB, 3), cp_H(NH, RB, CB, 3)>(re, im);
         if constexpr (SPLIT) relayout_split<T, R, RB, cp_S(NH, RB, CB, 3), cp_S(NH, RB, CB, 2)>(re, im, lds, tau);
@@ -459,6 +436,13 @@ static inline unsigned shift_reduce_grid(int64_t n_slots) {
 
 static inline int nacc_of(const QArgs &qa) { return qa.nq + 1; }
 static inline bool is_q2(const QArgs &qa) { return qa.nq == 1 && qa.q[0] == 2.0; }
+// QM of tile_sums for these indices
+static inline int q_mode(const QArgs &qa) {
+  if (is_q2(qa)) return 2;
+  for (int i = 0; i < qa.nq; ++i)
+    if (qa.q[i] != 1.0 && qa.q[i] != 2.0 && qa.q[i] != 3.0 && qa.q[i] != 4.0) return 0;
+  return 1;
+}
 // One workgroup per tile: the row and column kernels take tile tile0 + blockIdx.x only, in launches
 // of at most MAX_GRID workgroups (gridDim.x x blockDim.x must stay below 2^32; a multiple of 8, so
 // the XCD of a workgroup is blockIdx.x mod 8 in every chunk).
@@ -471,12 +455,13 @@ template <> struct ResidentRB<float> { static constexpr int value = 5; };
 template <> struct ResidentRB<double> { static constexpr int value = 4; };
 
 template <typename T, int NT, int RB, int NL, bool WRITE, bool SPLIT = false>
-static void launch_row_q(RowPassArgs A, bool q2, hipStream_t st) {
+static void launch_row_q(RowPassArgs A, int qm, hipStream_t st) {
   ProfScope prof(WRITE ? "sre_rowpass_write" : "sre_rowpass_resident", st);
   for (A.tile0 = 0; A.tile0 < A.n_tiles; A.tile0 += MAX_GRID) {
     const dim3 grid((unsigned)grid_for(A.n_tiles - A.tile0)), block(NT);
-    if (WRITE || !q2) hipLaunchKernelGGL((k_sre_rowpass<T, NT, RB, NL, WRITE, 0, SPLIT>), grid, block, 0, st, A);
-    else hipLaunchKernelGGL((k_sre_rowpass<T, NT, RB, NL, WRITE, 2, SPLIT>), grid, block, 0, st, A);
+    if (WRITE || qm == 0) hipLaunchKernelGGL((k_sre_rowpass<T, NT, RB, NL, WRITE, 0, SPLIT>), grid, block, 0, st, A);
+    else if (qm == 1) hipLaunchKernelGGL((k_sre_rowpass<T, NT, RB, NL, WRITE, WRITE ? 0 : 1, SPLIT>), grid, block, 0, st, A);
+    else hipLaunchKernelGGL((k_sre_rowpass<T, NT, RB, NL, WRITE, WRITE ? 0 : 2, SPLIT>), grid, block, 0, st, A);
   }
 }
 
@@ -489,12 +474,13 @@ static int64_t row_tiles(const RowPassArgs &A) {
 
 // Workgroup-resident row pass (one row = one whole folded shift vector of 2^NL values).
 template <typename T, int NT, int RB, int NL, int MINW>
-static void launch_row_occ(RowPassArgs A, bool q2, hipStream_t st) {
+static void launch_row_occ(RowPassArgs A, int qm, hipStream_t st) {
   ProfScope prof("sre_rowpass_resident", st);
   for (A.tile0 = 0; A.tile0 < A.n_tiles; A.tile0 += MAX_GRID) {
     const dim3 grid((unsigned)grid_for(A.n_tiles - A.tile0)), block(NT);
-    if (q2) hipLaunchKernelGGL((k_sre_rowpass_occ<T, NT, RB, NL, 2, MINW>), grid, block, 0, st, A);
-    else hipLaunchKernelGGL((k_sre_rowpass_occ<T, NT, RB, NL, 0, (MINW > 3 ? 3 : MINW)>), grid, block, 0, st, A);  // general q: more accumulators
+    if (qm == 2) hipLaunchKernelGGL((k_sre_rowpass_occ<T, NT, RB, NL, 2, MINW>), grid, block, 0, st, A);
+    else if (qm == 1) hipLaunchKernelGGL((k_sre_rowpass_occ<T, NT, RB, NL, 1, MINW>), grid, block, 0, st, A);
+    else hipLaunchKernelGGL((k_sre_rowpass_occ<T, NT, RB, NL, 0, (MINW > 3 ? 3 : MINW)>), grid, block, 0, st, A);
   }
 }
 
@@ -502,13 +488,13 @@ static void launch_row_occ(RowPassArgs A, bool q2, hipStream_t st) {
 // budget of at least 3 waves per SIMD (4 for 2^14 FP32 values: 512 threads x 32 values in 128
 // registers); one tile per workgroup, the tiles use about 100 registers.
 template <typename T>
-static int launch_resident(int NL, RowPassArgs A, bool q2, hipStream_t st, bool split = false) {
+static int launch_resident(int NL, RowPassArgs A, int qm, hipStream_t st, bool split = false) {
   constexpr int RB = ResidentRB<T>::value;
   if (split && NL >= 10 && NL <= 14) {
 #define HM_RO(nl, nt, w)                                            \
   case nl:                                                          \
     A.n_tiles = row_tiles<nt, RB, nl>(A);                           \
-    launch_row_occ<T, nt, RB, nl, w>(A, q2, st);                    \
+    launch_row_occ<T, nt, RB, nl, w>(A, qm, st);                    \
     return OK;
     if constexpr (RB == 5) {
       // one shift per workgroup from 2^11 values on (a one-wave workgroup at 2^11: measured 18.6 ->
@@ -522,17 +508,17 @@ static int launch_resident(int NL, RowPassArgs A, bool q2, hipStream_t st, bool 
 #define HM_RS(nl)                                                   \
   case nl:                                                          \
     A.n_tiles = row_tiles<64, nl, nl>(A);                           \
-    launch_row_q<T, 64, nl, nl, false>(A, q2, st);                  \
+    launch_row_q<T, 64, nl, nl, false>(A, qm, st);                  \
     return OK;
 #define HM_RR(nl, nt)                                               \
   case nl:                                                          \
     A.n_tiles = row_tiles<nt, RB, nl>(A);                           \
-    launch_row_q<T, nt, RB, nl, false>(A, q2, st);                  \
+    launch_row_q<T, nt, RB, nl, false>(A, qm, st);                  \
     return OK;
 #define HM_RX(nl, nt)                                               \
   case nl:                                                          \
     A.n_tiles = row_tiles<nt, RB, nl>(A);                           \
-    launch_row_q<T, nt, RB, nl, false, true>(A, q2, st);            \
+    launch_row_q<T, nt, RB, nl, false, true>(A, qm, st);            \
     return OK;
   if constexpr (RB == 5) {
     switch (NL) {
@@ -602,26 +588,27 @@ static int launch_rowwrite(int rb, int NL, RowPassArgs A, bool split, hipStream_
 }
 
 template <typename T, int NT, int RB, int NH, bool SPLIT>
-static void launch_col_nh(ColPassArgs A, bool q2, hipStream_t st) {
+static void launch_col_nh(ColPassArgs A, int qm, hipStream_t st) {
   constexpr int CB = ilog2c(NT) + RB - NH;
   A.n_cb = (int64_t)1 << (A.nl - CB);
   A.n_tiles = A.n_slots * A.n_cb;
   ProfScope prof("sre_colpass", st);
   for (A.tile0 = 0; A.tile0 < A.n_tiles; A.tile0 += MAX_GRID) {  // the first chunk also sums the previous batch
     const dim3 grid((unsigned)grid_for(A.n_tiles - A.tile0)), block(NT);
-    if (q2) hipLaunchKernelGGL((k_sre_colpass<T, NT, RB, NH, CB, 2, SPLIT>), grid, block, 0, st, A);
+    if (qm == 2) hipLaunchKernelGGL((k_sre_colpass<T, NT, RB, NH, CB, 2, SPLIT>), grid, block, 0, st, A);
+    else if (qm == 1) hipLaunchKernelGGL((k_sre_colpass<T, NT, RB, NH, CB, 1, SPLIT>), grid, block, 0, st, A);
     else hipLaunchKernelGGL((k_sre_colpass<T, NT, RB, NH, CB, 0, SPLIT>), grid, block, 0, st, A);
   }
 }
 
 // Column tiles of 2^col_tb values (col_tb - rb thread bits), RB register bits.
 template <typename T, int RB, int TBC, bool SPLIT>
-static int launch_col_tb(int NH, ColPassArgs &A, bool q2, hipStream_t st) {
+static int launch_col_tb(int NH, ColPassArgs &A, int qm, hipStream_t st) {
   constexpr int NT = 1 << (TBC - RB);
 #define HM_C(nh)                                                    \
   case nh:                                                          \
     if constexpr (nh >= RB && nh <= TBC) {                          \
-      launch_col_nh<T, NT, RB, nh, SPLIT>(A, q2, st);               \
+      launch_col_nh<T, NT, RB, nh, SPLIT>(A, qm, st);               \
       return OK;                                                    \
     }                                                               \
     break;
@@ -631,20 +618,20 @@ static int launch_col_tb(int NH, ColPassArgs &A, bool q2, hipStream_t st) {
 }
 
 template <typename T>
-static int launch_colpass(int rb, int col_tb, int NH, ColPassArgs &A, bool q2, bool split, hipStream_t st) {
+static int launch_colpass(int rb, int col_tb, int NH, ColPassArgs &A, int qm, bool split, hipStream_t st) {
   if (A.nl < col_tb - NH) return fail(E_UNSUPPORTED, "column pass: rows of 2^%d too short for 2^%d-row tiles", A.nl, NH);
   if constexpr (sizeof(T) == 4) {
     if (rb == 5 && col_tb == 13)
-      return split ? launch_col_tb<T, 5, 13, true>(NH, A, q2, st) : launch_col_tb<T, 5, 13, false>(NH, A, q2, st);
+      return split ? launch_col_tb<T, 5, 13, true>(NH, A, qm, st) : launch_col_tb<T, 5, 13, false>(NH, A, qm, st);
     if (rb == 5 && col_tb == 11)
-      return split ? launch_col_tb<T, 5, 11, true>(NH, A, q2, st) : launch_col_tb<T, 5, 11, false>(NH, A, q2, st);
-    if (rb == 4 && col_tb == 13 && !split) return launch_col_tb<T, 4, 13, false>(NH, A, q2, st);
-    if (rb == 4 && col_tb == 11 && !split) return launch_col_tb<T, 4, 11, false>(NH, A, q2, st);
+      return split ? launch_col_tb<T, 5, 11, true>(NH, A, qm, st) : launch_col_tb<T, 5, 11, false>(NH, A, qm, st);
+    if (rb == 4 && col_tb == 13 && !split) return launch_col_tb<T, 4, 13, false>(NH, A, qm, st);
+    if (rb == 4 && col_tb == 11 && !split) return launch_col_tb<T, 4, 11, false>(NH, A, qm, st);
   } else {
     if (rb == 4 && col_tb == 12)
-      return split ? launch_col_tb<T, 4, 12, true>(NH, A, q2, st) : launch_col_tb<T, 4, 12, false>(NH, A, q2, st);
+      return split ? launch_col_tb<T, 4, 12, true>(NH, A, qm, st) : launch_col_tb<T, 4, 12, false>(NH, A, qm, st);
     if (rb == 4 && col_tb == 10)
-      return split ? launch_col_tb<T, 4, 10, true>(NH, A, q2, st) : launch_col_tb<T, 4, 10, false>(NH, A, q2, st);
+      return split ? launch_col_tb<T, 4, 10, true>(NH, A, qm, st) : launch_col_tb<T, 4, 10, false>(NH, A, qm, st);
   }
   return fail(E_UNSUPPORTED, "column pass: tile 2^%d with RB %d (split %d) not built for this dtype", col_tb, rb,
               (int)split);
@@ -653,7 +640,7 @@ static int launch_colpass(int rb, int col_tb, int NH, ColPassArgs &A, bool q2, b
 template <typename T>
 int shift_sums_t(const SrePlan &p, const void *psi, const QArgs &qa, uint64_t a0, const uint64_t *rows,
                         int64_t n_slots, double *shift_sums, char *w, hipStream_t st) {
-  const bool q2 = is_q2(qa);
+  const int qm = q_mode(qa);
   const int nacc = nacc_of(qa);
   if (n_slots <= 0) return OK;
   if (p.path == 1) {
@@ -667,7 +654,7 @@ int shift_sums_t(const SrePlan &p, const void *psi, const QArgs &qa, uint64_t a0
     A.shift_sums = shift_sums;
     A.nacc = nacc;
     A.qa = qa;
-    int e = launch_resident<T>(p.nf, A, q2, st, p.split != 0);
+    int e = launch_resident<T>(p.nf, A, qm, st, p.split != 0);
     if (e) return e;
     return hipPeekAtLastError() == hipSuccess ? OK : fail(E_HIP, "SRE row pass launch: %s", hipGetErrorString(hipGetLastError()));
   }
@@ -737,7 +724,7 @@ int shift_sums_t(const SrePlan &p, const void *psi, const QArgs &qa, uint64_t a0
     C.prev_a0 = a0 + (uint64_t)ln.prev_s0;
     C.prev_rows = rows ? rows + ln.prev_s0 : nullptr;
     C.prev_shift_sums = shift_sums + ln.prev_s0 * nacc;
-    e = launch_colpass<T>(p.col_rb, p.col_tb, p.nh, C, q2, p.split != 0, ln.st);
+    e = launch_colpass<T>(p.col_rb, p.col_tb, p.nh, C, qm, p.split != 0, ln.st);
     if (e) return e;
     ln.prev_s0 = s0;
     ln.prev_nb = nb;
@@ -913,7 +900,7 @@ int states_t(const SrePlan &p, const void *const *psis, int n_states, const QArg
   A.n_states = n_states;
   A.state_bits = p.N;
   for (int i = 0; i < n_states; ++i) A.psis[i] = psis[i];
-  int e = launch_resident<T>(p.nf, A, is_q2(qa), st, p.split != 0);
+  int e = launch_resident<T>(p.nf, A, q_mode(qa), st, p.split != 0);
   if (e) return e;
   return hipPeekAtLastError() == hipSuccess ? OK : fail(E_HIP, "SRE batched launch: %s", hipGetErrorString(hipGetLastError()));
 }

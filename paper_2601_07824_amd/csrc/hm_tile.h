@@ -248,50 +248,134 @@ struct QArgs {
   double q[HM_MAX_Q];
 };
 
-// Per-real-value accumulation of the reduction of Algorithm 2: t = x^2 = |<P>|^2 (folded form),
-// acc[0] += t, acc[1+i] += t^{q_i} (q_i == 1: t log2 t).
-template <typename T, int QM> struct Acc {
-  static constexpr int N = (QM == 2) ? 2 : HM_MAX_Q + 1;
-  T a[N];
-  __device__ __forceinline__ void zero() {
+// Sums over the 2R real values x of a thread for the reduction of Algorithm 2, with t = x^2 = |<P>|^2
+// (folded form): kind 0 is sum t, otherwise sum t^q (q == 1: sum t log2 t).  The kind is uniform, so one
+// q at a time runs through the registers; the kinds that call a math function handle C registers per pass
+// of a loop that rotates the register arrays (back in place at its end): unrolled over all 2R values they
+// made kernels of 70 kB of code, which do not stay in the instruction cache.
+enum QKind { Q_NORM = 0, Q_SHANNON, Q_TWO, Q_THREE, Q_FOUR, Q_POW };
+__device__ __forceinline__ QKind q_kind(double q) {
+  return q == 1.0 ? Q_SHANNON : q == 2.0 ? Q_TWO : q == 3.0 ? Q_THREE : q == 4.0 ? Q_FOUR : Q_POW;
+}
+// FENCE > 0: a scheduling fence after every FENCE registers (bounds the temporaries in flight).
+template <typename T, int R, int FENCE = 0, typename F>
+__device__ __forceinline__ void each_real(T (&re)[R], T (&im)[R], F f) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) a[i] = T(0);
+  for (int r = 0; r < R; ++r) {
+    f(re[r]);
+    f(im[r]);
+    if constexpr (FENCE > 0) {
+      if ((r + 1) % FENCE == 0) __builtin_amdgcn_sched_barrier(0);
+    }
   }
-  __device__ __forceinline__ void add(T x, const QArgs &qa) {
-    const T t = x * x;
-    a[0] += t;
-    if constexpr (QM == 2) {
-      a[1] = fmaT(t, t, a[1]);
-    } else {
+}
+template <typename T, int R, int C, int FENCE, typename F>
+__device__ __forceinline__ void each_real_rotating(T (&re)[R], T (&im)[R], F f) {
+  static_assert(R % C == 0, "whole passes");
+  if constexpr (C == R) {
+    each_real<T, R, FENCE>(re, im, f);
+  } else {
+#pragma unroll 1
+    for (int p = 0; p < R / C; ++p) {
 #pragma unroll
-      for (int i = 0; i < HM_MAX_Q; ++i) {
-        if (i < qa.nq) {
-          const double q = qa.q[i];
-          T v;
-          if (q == 1.0) v = t > T(0) ? t * (T)log2(t) : T(0);
-          else if (q == 2.0) v = t * t;
-          else if (q == 3.0) v = t * t * t;
-          else if (q == 4.0) { T t2 = t * t; v = t2 * t2; }
-          else v = t > T(0) ? (T)pow(t, (T)q) : T(0);
-          a[1 + i] += v;
-        }
+      for (int r = 0; r < C; ++r) {
+        f(re[r]);
+        f(im[r]);
+        if ((r + 1) % FENCE == 0) __builtin_amdgcn_sched_barrier(0);
+      }
+      T hr[C], hi[C];
+#pragma unroll
+      for (int r = 0; r < C; ++r) {
+        hr[r] = re[r];
+        hi[r] = im[r];
+      }
+#pragma unroll
+      for (int r = 0; r + C < R; ++r) {
+        re[r] = re[r + C];
+        im[r] = im[r + C];
+      }
+#pragma unroll
+      for (int r = 0; r < C; ++r) {
+        re[R - C + r] = hr[r];
+        im[R - C + r] = hi[r];
       }
     }
   }
-};
-
-// Scale folded per-shift sums to the unfolded convention: a != 0 shifts were folded on one bit,
-// |chi|^2 = f t with f = 4; the a == 0 shift is folded without the factor (f = 1).
-__device__ __forceinline__ void unfold_scale(double *s, int nacc, const QArgs &qa, bool a_is_zero) {
-  if (a_is_zero) return;
-  const double f = 4.0;
-  const double s0 = s[0];
-  s[0] = f * s0;
-  for (int i = 0; i < qa.nq && 1 + i < nacc; ++i) {
-    const double q = qa.q[i];
-    if (q == 1.0) s[1 + i] = f * (s[1 + i] + 2.0 * s0);  // f (sum t log2 t + log2(f) sum t)
-    else s[1 + i] = exp2(2.0 * q) * s[1 + i];
+}
+template <typename T, int R, bool POW>
+__device__ __forceinline__ T sum_kind(T (&re)[R], T (&im)[R], QKind kind, double q) {
+#pragma clang fp contract(off)
+  T a = T(0);
+  switch (kind) {
+    case Q_NORM: each_real(re, im, [&](T x) { a += x * x; }); break;
+    case Q_TWO: each_real(re, im, [&](T x) { const T t = x * x; a += t * t; }); break;
+    case Q_THREE: each_real(re, im, [&](T x) { const T t = x * x; a += t * t * t; }); break;
+    case Q_SHANNON: {
+      // the FP32 log2 is a few instructions, the FP64 one about 80
+      constexpr int C = sizeof(T) == 4 || R < 4 ? R : 4;
+      each_real_rotating<T, R, C, 2>(re, im, [&](T x) {
+        const T t = x * x;
+        a += t > T(0) ? t * (T)log2(t) : T(0);
+      });
+      break;
+    }
+    case Q_FOUR: each_real(re, im, [&](T x) { const T t = x * x, t2 = t * t; a += t2 * t2; }); break;
+    default:
+      if constexpr (POW) {
+        each_real_rotating<T, R, 1, 1>(re, im, [&](T x) {
+          const T t = x * x;
+          a += t > T(0) ? (T)pow(t, (T)q) : T(0);
+        });
+      }
+      break;
   }
+  return a;
+}
+
+// The sums of a tile's segments of SEG threads (seg_sum): out(k, s) is called by every thread for k = 0 ..
+// nacc - 1 in turn and gets the segment's total in the segment's first thread.  QM == 2: q = (2); QM == 1:
+// every q is 1, 2, 3 or 4 (pow's temporaries would not fit beside the values of the largest tiles);
+// QM == 0: any q.  Measured for q = (1, 2, 3) on MI355X against all kinds unrolled with one accumulator
+// per q: complex64 N = 13 142 -> 78 us, N = 16 11.3 -> 6.3 ms; complex128 N = 15 15.6 -> 10.5 ms.
+template <typename T, int R, int NT, int SEG, int QM, typename F>
+__device__ __forceinline__ void tile_sums(T (&re)[R], T (&im)[R], const QArgs &qa, double *red, uint32_t tau, F out) {
+  if constexpr (QM == 2) {
+    T a0 = T(0), a1 = T(0);
+    each_real(re, im, [&](T x) {
+      const T t = x * x;
+      a0 += t;
+      a1 = fmaT(t, t, a1);
+    });
+    const double s0 = seg_sum<NT, SEG>((double)a0, red, tau), s1 = seg_sum<NT, SEG>((double)a1, red, tau);
+    out(0, s0);
+    out(1, s1);
+  } else {
+#pragma unroll 1
+    for (int k = 0; k <= qa.nq; ++k) {
+      const double q = k ? qa.q[k - 1] : 1.0;
+      // the values are the same for every k: keep the compiler from holding their squares across the loop
+#pragma unroll
+      for (int r = 0; r < R; ++r) asm volatile("" : "+v"(re[r]), "+v"(im[r]));
+      const T a = sum_kind<T, R, QM == 0>(re, im, k ? q_kind(q) : Q_NORM, q);
+      out(k, seg_sum<NT, SEG>((double)a, red, tau));
+    }
+  }
+}
+
+// Scale folded per-shift sum k to the unfolded convention: a != 0 shifts were folded on one bit,
+// |chi|^2 = f t with f = 4; the a == 0 shift is folded without the factor (f = 1).  s0 is the folded
+// sum 0.
+__device__ __forceinline__ double unfold_sum(int k, double s, double s0, const QArgs &qa, bool a_is_zero) {
+  if (a_is_zero) return s;
+  const double f = 4.0;
+  if (k == 0) return f * s;
+  const double q = qa.q[k - 1];
+  return q == 1.0 ? f * (s + 2.0 * s0)  // f (sum t log2 t + log2(f) sum t)
+                  : exp2(2.0 * q) * s;
+}
+__device__ __forceinline__ void unfold_scale(double *s, int nacc, const QArgs &qa, bool a_is_zero) {
+  const double s0 = s[0];
+  for (int k = 0; k < nacc; ++k) s[k] = unfold_sum(k, s[k], s0, qa, a_is_zero);
 }
 
 }  // namespace hm
