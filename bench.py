@@ -196,11 +196,11 @@ def exchange_roofline(prof, fam_bytes: dict, work_values: float):
 
 def mixed_pass_bytes(na: int, value_bytes: int = 16) -> float:
     """Bytes the mixed-state mana streams through HBM: the first pass reads rho and writes the
-    reordered copy (qutrits 0..2), each further pass but the last reads and writes it (two qutrits),
-    the last reads it; 9^na values each time."""
+    reordered copy (qutrits 0..2), each further pass but the last reads and writes it (up to three
+    qutrits), the last reads it; 9^na values each time."""
     m = min(na, 3)
     rest = na - m
-    passes = (rest + 1) // 2
+    passes = (rest + 2) // 3
     units = (1 if passes == 0 else 2) + 2 * max(passes - 1, 0) + (1 if passes else 0)
     return units * 9.0 ** na * value_bytes
 

@@ -7,14 +7,17 @@
 // qutrit k = base-3 digit k of r and c) is reordered so that qutrit k's pair (r_k, c_k) is the base-9
 // digit k of the position (p = sum_k (3 r_k + c_k) 9^k), and the single-qutrit matrix is applied along
 // every digit.  Several digits share one HBM-streaming pass through LDS:
-//   * pass A reads a 27 x 27 block of rho (qutrits 0..2 of its rows and columns vary, 27 contiguous
-//     columns per row), reorders it in LDS, applies the matrix along digits 0, 1, 2 and writes the
-//     729 values contiguously (the reordering costs no pass of its own);
-//   * each pass B takes digits k, k + 1 with digit 0 along for contiguous 144-B segments (9 x 81
-//     values per tile), in place (a last single digit takes digits 0 and 1 along);
+//   * the first pass reads a 27 x 27 block of rho (qutrits 0..2 of its rows and columns vary, 27
+//     contiguous columns per row), applies the matrix along digits 0, 1, 2 and writes the 729 values
+//     contiguously in digit order (the reordering costs no pass of its own);
+//   * each further pass takes up to three digits k .. k + ND - 1 with J contiguous lower positions along
+//     for the coalescing, in place: the first digit is transformed on the way in (a thread loads whole
+//     fibres), the last on the way out, so LDS holds the tile between two digits only;
 //   * the last pass does not write back: it reduces sum_u |w_u|, sum_u w_u and sum_u w_u^2 in FP64
 //     (fixed order) instead.
-// N = 8 thus streams the 9^N values 4 times (read + write 3 times, read once) instead of N + 1.
+// The passes are bound by HBM (read and write rate of a plain copy 4.75 TB/s), so their number decides:
+// N = 8 streams the 9^N values 3 times (read + write twice, read once).  With at most two digits per later
+// pass it was 4 times: N = 8 complex128 1019 us then, 740 us now.
 //
 // The single-qutrit matrix, from A_ab|x> = omega^{2b(a-x)} |2a - x> (the phase-space point operators of
 // Eq. phase-space up to a relabelling of the points): with x_mu = rho_{r,c} at mu = 3 r + c,
@@ -60,26 +63,30 @@ __device__ __forceinline__ void mixed_fibre(const vec2<T> (&x)[9], vec2<T> (&y)[
 static constexpr int MIXED_NT = 256;
 static constexpr int MIXED_RED_BLOCKS = 2048;
 
-// Fibres of 9 values at stride `st` inside an LDS tile: fibre f (f < nfib) starts at
-// (f / st) * 9 st + f % st; thread t takes fibres t, t + MIXED_NT, ...
-template <typename T>
-__device__ __forceinline__ void lds_digit(vec2<T> *t, int nfib, int st) {
-  for (int f = threadIdx.x; f < nfib; f += MIXED_NT) {
-    const int base = (f / st) * st * 9 + f % st;
+// Fibres of 9 values at stride ST inside an LDS tile of NF fibres: fibre f starts at
+// (f / ST) * 9 ST + f % ST; thread t takes fibres t, t + MIXED_NT, ...
+template <int ST>
+__device__ __forceinline__ int fibre_base(int f) {
+  return (f / ST) * ST * 9 + f % ST;
+}
+template <typename T, int NF, int ST>
+__device__ __forceinline__ void lds_digit(vec2<T> *t) {
+  for (int f = threadIdx.x; f < NF; f += MIXED_NT) {
+    const int base = fibre_base<ST>(f);
     vec2<T> x[9], y[9];
 #pragma unroll
-    for (int a = 0; a < 9; ++a) x[a] = t[base + a * st];
+    for (int a = 0; a < 9; ++a) x[a] = t[base + a * ST];
     mixed_fibre<T>(x, y);
 #pragma unroll
-    for (int a = 0; a < 9; ++a) t[base + a * st] = y[a];
+    for (int a = 0; a < 9; ++a) t[base + a * ST] = y[a];
   }
 }
-
-// FP64 sums {sum |w|, sum w, sum w^2} of the real parts of the tile's n values into acc.
+// The fibre sums {sum |w|, sum w, sum w^2} of the real parts into acc (FP64).
 template <typename T>
-__device__ __forceinline__ void lds_sums(const vec2<T> *t, int n, double (&acc)[3]) {
-  for (int e = threadIdx.x; e < n; e += MIXED_NT) {
-    const double w = (double)t[e].x;  // real for a Hermitian rho
+__device__ __forceinline__ void fibre_sums(const vec2<T> (&y)[9], double (&acc)[3]) {
+#pragma unroll
+  for (int a = 0; a < 9; ++a) {
+    const double w = (double)y[a].x;  // real for a Hermitian rho
     acc[0] += fabs(w);
     acc[1] += w;
     acc[2] = fma(w, w, acc[2]);
@@ -100,16 +107,18 @@ __device__ __forceinline__ void block_sums_out(double (&acc)[3], double *part) {
     for (int k = 0; k < 3; ++k) part[blockIdx.x * 3 + k] = red[k][0];
 }
 
-// Pass A: tile q (q < 9^(N - M)) is the 3^M x 3^M block of rho whose rows and columns share the
-// base-3 digits M.. of q's pairs (mu_k = 3 r_k + c_k = base-9 digit k - M of q); in LDS it is
-// reordered to p_lo = sum_{j < M} mu_j 9^j and transformed along digits 0..M-1, then written to
-// v[q 9^M + p_lo] (REDUCE: summed instead).  M = min(N, 3).
+// First pass: tile q (q < 9^(N - M)) is the 3^M x 3^M block of rho whose rows and columns share the
+// base-3 digits M.. of q's pairs (mu_k = 3 r_k + c_k = base-9 digit k - M of q).  A thread loads the 3 x 3
+// entries of a digit-0 fibre, transforms and stores them at p_lo = sum_{j < M} mu_j 9^j in LDS; digits 1 ..
+// M - 1 follow there, the last of them on the way to v[q 9^M + p_lo] (REDUCE: into the sums instead).
+// M = min(N, 3).
 template <typename T, int M, bool REDUCE>
 __global__ __launch_bounds__(MIXED_NT) void k_mixed_first(const vec2<T> *__restrict__ rho, uint64_t D, uint64_t n_tiles,
                                                            vec2<T> *__restrict__ v, double *part) {
   constexpr int B = M == 1 ? 3 : M == 2 ? 9 : 27;  // 3^M
   constexpr int TILE = B * B;                       // 9^M
-  __shared__ vec2<T> t[TILE];
+  constexpr int NF = TILE / 9, LST = TILE / 9;      // fibres; stride of the last digit
+  __shared__ vec2<T> t[M > 1 ? TILE : 1];
   double acc[3] = {0.0, 0.0, 0.0};
   for (uint64_t b = blockIdx.x; b < n_tiles; b += gridDim.x) {
     // neighbouring blocks share cache lines at their edges: keep them on one XCD's L2
@@ -123,69 +132,106 @@ __global__ __launch_bounds__(MIXED_NT) void k_mixed_first(const vec2<T> *__restr
       C += (mu % 3) * w3;
       w3 *= 3;
     }
-    __syncthreads();  // the previous tile's LDS reads are done
-    for (int e = threadIdx.x; e < TILE; e += MIXED_NT) {
-      const int rl = e / B, cl = e % B;  // row-major within the block: B contiguous columns per row
-      int p = 0, w9 = 1, r = rl, c = cl;
+    vec2<T> *o = v + q * TILE;
+    auto put = [&](const vec2<T>(&y)[9], int base) {
+      if constexpr (REDUCE) {
+        fibre_sums<T>(y, acc);
+      } else {
 #pragma unroll
-      for (int j = 0; j < M; ++j, w9 *= 9, r /= 3, c /= 3) p += (3 * (r % 3) + (c % 3)) * w9;
-      t[p] = rho[(R + rl) * D + C + cl];
+        for (int a = 0; a < 9; ++a) o[base + a * LST] = y[a];
+      }
+    };
+    if constexpr (M > 1) __syncthreads();  // the previous tile's LDS reads are done
+    for (int f = threadIdx.x; f < NF; f += MIXED_NT) {
+      // fibre f: row group f / (B / 3), column group f % (B / 3) (the digits above digit 0)
+      const int rg = f / (B / 3), cg = f % (B / 3);
+      vec2<T> x[9], y[9];
+      const vec2<T> *src = rho + (R + 3 * rg) * D + C + 3 * cg;
+#pragma unroll
+      for (int a = 0; a < 9; ++a) x[a] = src[(a / 3) * D + a % 3];
+      mixed_fibre<T>(x, y);
+      int p = 0, w9 = 9, r = rg, c = cg;
+#pragma unroll
+      for (int j = 1; j < M; ++j, w9 *= 9, r /= 3, c /= 3) p += (3 * (r % 3) + (c % 3)) * w9;
+      if constexpr (M == 1) {
+        put(y, p);
+      } else {
+#pragma unroll
+        for (int a = 0; a < 9; ++a) t[p + a] = y[a];
+      }
     }
-    __syncthreads();
-    lds_digit<T>(t, TILE / 9, 1);
-    if constexpr (M >= 2) {
+    if constexpr (M == 3) {
       __syncthreads();
-      lds_digit<T>(t, TILE / 9, 9);
+      lds_digit<T, NF, 9>(t);
     }
-    if constexpr (M >= 3) {
+    if constexpr (M > 1) {
       __syncthreads();
-      lds_digit<T>(t, TILE / 9, 81);
-    }
-    __syncthreads();
-    if constexpr (REDUCE) {
-      lds_sums<T>(t, TILE, acc);
-    } else {
-      vec2<T> *o = v + q * TILE;
-      for (int e = threadIdx.x; e < TILE; e += MIXED_NT) o[e] = t[e];
+      for (int f = threadIdx.x; f < NF; f += MIXED_NT) {
+        vec2<T> x[9], y[9];
+        const int base = fibre_base<LST>(f);
+#pragma unroll
+        for (int a = 0; a < 9; ++a) x[a] = t[base + a * LST];
+        mixed_fibre<T>(x, y);
+        put(y, base);
+      }
     }
   }
   if constexpr (REDUCE) block_sums_out(acc, part);
 }
 
-// Pass B: digits k and k + 1 (ND = 2) or k alone (ND = 1), with the P lowest digits carried along
-// so that a tile reads contiguous segments of 9^P values (144 B for P = 1, 1296 B for P = 2) and
-// holds 9^(ND + P) = 729 values: tile q covers base + j + sum_{i < ND} mu_i 9^(k + i), j < 9^P,
-// base = (q mod 9^(k-P)) 9^P + (q div 9^(k-P)) 9^(k+ND); LDS layout [mu_{k+1}][mu_k][j].  In place,
-// or summed (REDUCE).
-template <typename T, int ND, int P, bool REDUCE>
-__global__ __launch_bounds__(MIXED_NT) void k_mixed_pair(vec2<T> *__restrict__ v, uint64_t n_tiles, uint64_t lo_span,
-                                                          uint64_t stride_k, double *part) {
-  constexpr int PS = P == 1 ? 9 : 81;           // 9^P
-  constexpr int TILE = PS * (ND == 2 ? 81 : 9);  // 9^(ND + P)
-  __shared__ vec2<T> t[TILE];
+// Later pass: digits k .. k + ND - 1 (S = 9^k their lowest stride), J contiguous positions below them along
+// (J divides S): tile q covers base + j + m S, j < J, m < 9^ND, base = (q mod (S / J)) J + (q div (S / J)) 9^ND S;
+// LDS layout [m][j].  In place, or summed (REDUCE).
+template <typename T, int ND, int J, bool REDUCE>
+__global__ __launch_bounds__(MIXED_NT) void k_mixed_pass(vec2<T> *__restrict__ v, uint64_t n_tiles, uint64_t n_lo,
+                                                          uint64_t S, double *part) {
+  constexpr int P9 = ND == 1 ? 9 : ND == 2 ? 81 : 729;  // 9^ND
+  constexpr int TILE = J * P9, NF = TILE / 9, LST = NF;
+  __shared__ vec2<T> t[ND > 1 ? TILE : 1];
   double acc[3] = {0.0, 0.0, 0.0};
-  auto off = [&](int e) -> uint64_t {
-    const int j = e % PS, m = e / PS;  // m = mu_k + 9 mu_{k+1}
-    return (uint64_t)j + (ND == 2 ? (uint64_t)(m % 9) * stride_k + (uint64_t)(m / 9) * stride_k * 9
-                                  : (uint64_t)m * stride_k);
-  };
   for (uint64_t b = blockIdx.x; b < n_tiles; b += gridDim.x) {
     // consecutive tiles share the cache lines their segments straddle: keep them on one XCD's L2
     const uint64_t q = (uint64_t)xcd_tile((int64_t)b, (int64_t)n_tiles);
-    const uint64_t base = (q % lo_span) * PS + (q / lo_span) * stride_k * (ND == 2 ? 81 : 9);
-    __syncthreads();
-    for (int e = threadIdx.x; e < TILE; e += MIXED_NT) t[e] = v[base + off(e)];
-    __syncthreads();
-    lds_digit<T>(t, TILE / 9, PS);
-    if constexpr (ND == 2) {
-      __syncthreads();
-      lds_digit<T>(t, TILE / 9, PS * 9);
+    vec2<T> *w = v + (q % n_lo) * J + (q / n_lo) * S * P9;
+    auto at = [&](int e) -> vec2<T> * { return w + (e % J) + (uint64_t)(e / J) * S; };  // LDS position e
+    auto put = [&](const vec2<T>(&y)[9], int base) {
+      if constexpr (REDUCE) {
+        fibre_sums<T>(y, acc);
+      } else {
+        vec2<T> *o = at(base);
+#pragma unroll
+        for (int a = 0; a < 9; ++a) o[(uint64_t)a * (LST / J) * S] = y[a];
+      }
+    };
+    if constexpr (ND > 1) __syncthreads();
+    for (int f = threadIdx.x; f < NF; f += MIXED_NT) {
+      vec2<T> x[9], y[9];
+      const int base = fibre_base<J>(f);
+      const vec2<T> *src = at(base);
+#pragma unroll
+      for (int a = 0; a < 9; ++a) x[a] = src[(uint64_t)a * S];
+      mixed_fibre<T>(x, y);
+      if constexpr (ND == 1) {
+        put(y, base);
+      } else {
+#pragma unroll
+        for (int a = 0; a < 9; ++a) t[base + a * J] = y[a];
+      }
     }
-    __syncthreads();
-    if constexpr (REDUCE) {
-      lds_sums<T>(t, TILE, acc);
-    } else {
-      for (int e = threadIdx.x; e < TILE; e += MIXED_NT) v[base + off(e)] = t[e];
+    if constexpr (ND == 3) {
+      __syncthreads();
+      lds_digit<T, NF, 9 * J>(t);
+    }
+    if constexpr (ND > 1) {
+      __syncthreads();
+      for (int f = threadIdx.x; f < NF; f += MIXED_NT) {
+        vec2<T> x[9], y[9];
+        const int base = fibre_base<LST>(f);
+#pragma unroll
+        for (int a = 0; a < 9; ++a) x[a] = t[base + a * LST];
+        mixed_fibre<T>(x, y);
+        put(y, base);
+      }
     }
   }
   if constexpr (REDUCE) block_sums_out(acc, part);
@@ -264,6 +310,19 @@ static void launch_first(bool reduce, const void *rho, uint64_t D, uint64_t tile
   }
 }
 
+template <typename T, int ND, int J>
+static void launch_pass(bool reduce, uint64_t V, int k, vec2<T> *v, double *part, unsigned *red_grid, hipStream_t st) {
+  const uint64_t S = pow_u(9, k), tiles = V / (pow_u(9, ND) * J);
+  ProfScope prof(reduce ? "mixed_last" : "mixed_pass", st);
+  if (reduce) {
+    *red_grid = grid_of(tiles, MIXED_RED_BLOCKS);
+    hipLaunchKernelGGL((k_mixed_pass<T, ND, J, true>), dim3(*red_grid), dim3(MIXED_NT), 0, st, v, tiles, S / J, S, part);
+  } else {
+    hipLaunchKernelGGL((k_mixed_pass<T, ND, J, false>), dim3(grid_of(tiles, 1u << 20)), dim3(MIXED_NT), 0, st, v, tiles,
+                       S / J, S, part);
+  }
+}
+
 template <typename T>
 static int mixed_t(int N, const void *rho, double *out, void *ws, hipStream_t st) {
   const uint64_t D = pow_u(3, N), V = D * D;
@@ -276,24 +335,15 @@ static int mixed_t(int N, const void *rho, double *out, void *ws, hipStream_t st
   if (M == 1) launch_first<T, 1>(N == M, rho, D, tiles_a, v, part, &red_grid, st);
   else if (M == 2) launch_first<T, 2>(N == M, rho, D, tiles_a, v, part, &red_grid, st);
   else launch_first<T, 3>(N == M, rho, D, tiles_a, v, part, &red_grid, st);
+  // The remaining digits in as few passes as three digits each allow (four left: two and two).  Three
+  // digits carry 9 positions (144 / 72-byte segments, 105 / 52 KB of LDS; with 3 positions N = 9 took 7.1
+  // instead of 6.7 ms in complex128 and 4.8 instead of 3.6 in complex64).
   for (int k = M; k < N;) {
-    // two digits with digit 0 carried along, or (the last digit alone) one with digits 0 and 1
-    const int nd = N - k >= 2 ? 2 : 1, P = nd == 2 ? 1 : 2;
-    const bool last = k + nd == N;
-    const uint64_t tiles = V / pow_u(9, nd + P), lo_span = pow_u(9, k - P), stride_k = pow_u(9, k);
-    ProfScope prof(last ? "mixed_last" : "mixed_pair", st);
-    if (last) {
-      red_grid = grid_of(tiles, MIXED_RED_BLOCKS);
-      if (nd == 2)
-        hipLaunchKernelGGL((k_mixed_pair<T, 2, 1, true>), dim3(red_grid), dim3(MIXED_NT), 0, st, v, tiles, lo_span,
-                           stride_k, part);
-      else
-        hipLaunchKernelGGL((k_mixed_pair<T, 1, 2, true>), dim3(red_grid), dim3(MIXED_NT), 0, st, v, tiles, lo_span,
-                           stride_k, part);
-    } else {
-      hipLaunchKernelGGL((k_mixed_pair<T, 2, 1, false>), dim3(grid_of(tiles, 1u << 20)), dim3(MIXED_NT), 0, st, v, tiles,
-                         lo_span, stride_k, part);
-    }
+    const int left = N - k, nd = left == 4 ? 2 : left < 3 ? left : 3;
+    const bool last = left == nd;
+    if (nd == 3) launch_pass<T, 3, 9>(last, V, k, v, part, &red_grid, st);
+    else if (nd == 2) launch_pass<T, 2, 27>(last, V, k, v, part, &red_grid, st);
+    else launch_pass<T, 1, 243>(last, V, k, v, part, &red_grid, st);
     k += nd;
   }
   hipLaunchKernelGGL(k_mixed_total, dim3(1), dim3(256), 0, st, (const double *)part, (int)red_grid, N, out);
