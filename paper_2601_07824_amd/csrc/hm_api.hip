@@ -442,16 +442,35 @@ hm_status hm_sre_batched_grad(hm_handle h, const void *const *psis, const int *n
   return HM_OK;
 }
 
-// Default launch form of the batched forward (HM_OPT_BATCH_LAUNCH).
-static constexpr int BATCH_LAUNCH_DEFAULT = 1;
+// Launch form of the batched forward where neither HM_OPT_BATCH_LAUNCH nor the autotuner chose one.
+// The launches per size class run each n with its own workgroup size and register budget, about 1.2e12
+// Pauli strings/s; the persistent launch runs every shape at the occupancy of its largest tile, about
+// 0.6e12/s, but is one launch, where the classes cost two launches (about 10 us) per 64 states of a class.
+// So the classes win once their strings outweigh their launches.  Measured on MI355X (complex64, persistent
+// against classes): 48 states n = 9..14 2663 / 1514 us, 16 states n = 12..13 634 / 349, 64 states n = 11 288 /
+// 134, 60 states n = 7..11 97 / 93; 8 states n = 7..11 34 / 58, 1000 states n = 5..9 1006 / 1607.
+static int batched_auto_mode(hm_handle h, const int *ns, int batch, int dbl) {
+  double strings = 0.0;  // of the states the persistent launch could take
+  int count[32] = {};
+  for (int i = 0; i < batch; ++i) {
+    SrePlan p;
+    if (sre_plan(ns[i], dbl, plan_opts(h, ns[i], dbl), &p) != OK || p.path != 1 || !batch_resident_ok(ns[i], dbl)) continue;
+    strings += ldexp(1.0, 2 * ns[i]);
+    ++count[ns[i]];
+  }
+  int launches = 0;
+  for (int n = 0; n < 32; ++n) launches += (count[n] + HM_BATCH_PTRS - 1) / HM_BATCH_PTRS;
+  return strings > 1.2e7 * (launches - 1) ? 2 : 1;
+}
 
-// Batched calls: states of workgroup-resident size (path 1 under the handle's options, at least
-// 2^RB folded values) go to one persistent launch; the rest (tiny states, two-pass sizes) run by
-// size class / one after another on the same workspace after it.
+// Batched calls in the persistent form: states of workgroup-resident size (path 1 under the handle's
+// options, at least 2^RB folded values) go to one persistent launch; the rest (tiny states, two-pass
+// sizes; all states in the per-class form) run by size class / one after another on the same workspace
+// after it.
 static void batched_split(hm_handle h, const int *ns, int batch, int dbl, std::vector<int> *pers,
                           std::vector<int> *rest) {
   const int mode = h->opts.batch_launch ? h->opts.batch_launch
-                   : h->tuned_batch_launch ? h->tuned_batch_launch : BATCH_LAUNCH_DEFAULT;
+                   : h->tuned_batch_launch ? h->tuned_batch_launch : batched_auto_mode(h, ns, batch, dbl);
   for (int i = 0; i < batch; ++i) {
     if (mode == 2) {
       rest->push_back(i);
