@@ -275,28 +275,35 @@ __global__ __launch_bounds__(NT) void k_mana_rowpass(ManaRowArgs A) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Two-pass row pass: for one shift pair (a, a + 1) and G consecutive rows xh of 3^NL values, the
-// packed product v(a) + i v(a + 1) of each row followed by the NL radix-3 stages over the row index,
-// written to the exchange buffer.
+// Two-pass row pass: for six consecutive shifts (three shift pairs) and G consecutive rows xh of 3^NL
+// values, the packed products v(a) + i v(a') of each row followed by the NL radix-3 stages over the row
+// index, written to the exchange buffer.
 //
-// The shift pair is uniform over the workgroup, so the source index of every register splits into
-//   (row part: depends on the thread's row g) + (thread part: the thread's low S0 trits)
-//   + (register part: the register's trits minus the shift's digits, the same for every lane),
+// The row pass used to wait on its gathers: four amplitudes (32 B) per packed value, which the L2 serves
+// at about 28 B per CU and clock.  Shifts that differ in the lowest trit only read the same amplitudes:
+// with that trit among a thread's register trits, alpha_x = psi_{x - a} and alpha_{-x} of all three shifts
+// of a family 3 m, 3 m + 1, 3 m + 2 are renamings of one set of registers.  So a workgroup gathers two
+// families for three pairs (A0 A1, A2 B0, B1 B2): a third of the gathers, and the three values of the
+// lowest trit are contiguous.  (Rows of 3^6 at n = 12, per packed value: 69.1 us per 47 pairs before,
+// 47.7 us per 45 pairs now, n = 12 604 -> 470 ms.)
+//
+// The shifts are uniform over the workgroup, so the source index of every register splits into
+//   (row part: depends on the thread's row g) + (thread part: row trits 1 .. S0) + (register part: row
+//   trits S0 + 1 .. minus the shift's digits, the same for every lane),
 // where every part is digit-wise (x - a) mod 3 or (-x - a) mod 3.  The register part is computed
 // with scalar instructions and enters the loads as their uniform offset; the row and thread parts
 // come from per-thread tables of the three possible digit results per trit (8 bits each), one
-// bit-field extract per trit and shift.  So each packed value costs two loads per shift and no
-// vector instruction for its address.
-struct ManaWriteArgs {
+// bit-field extract per trit and family.
+struct ManaFamilyArgs {
   const void *psi;
   uint32_t psi_bytes;  // 3^N values
   int nhq;             // row-index trits above the tile's G rows (nh - log3 G)
   uint32_t nhr;        // 3^nh rows per pair
-  int64_t n_pairs;     // pairs in this launch
-  uint64_t a0;         // first shift of pair 0
-  uint64_t a_end;      // shifts >= a_end are absent
-  void *exch;          // [n_pairs][3^nh][3^NL]
-  int64_t n_tiles;     // (3^nh / G) * n_pairs
+  int64_t n_six;       // sextets of shifts in this launch: three pairs each
+  uint64_t a_base;     // first shift of sextet 0, a multiple of 3
+  uint64_t a_lo, a_end;  // shifts outside [a_lo, a_end) are absent (zero)
+  void *exch;          // [3 n_six][3^nh][3^NL]
+  int64_t n_tiles;     // (3^nh / G) * n_six
 };
 
 // Table of the three results ((x - h) mod 3) p (neg: ((-x - h) mod 3) p) for h = 0, 1, 2, 8 bits each.
@@ -307,12 +314,212 @@ __device__ __forceinline__ uint32_t trit_table(uint32_t x, uint32_t p, bool neg)
   return t;
 }
 
-// Register budget of the FP32 two-pass kernels: at least four waves per SIMD (row pass 118 and
-// column pass 96 VGPRs, no spills; measured at n = 12 on MI355X: row pass 74.3 -> 71.3 us, column
-// pass 38.2 -> 37.7 us per launch against the compiler's own budget; five or more waves spill).
+// Register budget of the FP32 two-pass kernels: four waves per SIMD (the column pass has 96 VGPRs, no spills:
+// 38.2 -> 37.7 us per launch at n = 12 against the compiler's own budget).  The family row pass reaches
+// them with 3^2 values per thread; with 3^3 it needs about 180 registers, two waves per SIMD, and waits on
+// its gathers again (n = 12, 45 pairs: 54 us against 48 in spite of one re-layout less).
 template <typename T> struct ManaWaves {
   static constexpr int row = sizeof(T) == 4 ? 4 : 1;
   static constexpr int col = sizeof(T) == 4 ? 4 : 1;
+};
+
+// The three values of the lowest trit at byte offset voff + soff (contiguous).
+__device__ __forceinline__ void buf_ld3(float2 *v, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  const float4 q = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
+  v[0] = float2{q.x, q.y};
+  v[1] = float2{q.z, q.w};
+  v[2] = buf_ld((float2 *)nullptr, r, voff + 16u, soff);
+}
+__device__ __forceinline__ void buf_ld3(double2 *v, __amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+#pragma unroll
+  for (uint32_t i = 0; i < 3; ++i) v[i] = buf_ld((double2 *)nullptr, r, voff + 16u * i, soff);
+}
+
+// Product of one shift of a gathered family, lowest trit H: conj(alpha_x) alpha_{-x} into the pair's first
+// place (SECOND: times i, added).
+template <typename T, int R, int H, bool SECOND>
+__device__ __forceinline__ void mana_product(const vec2<T> (&pm)[R], const vec2<T> (&pn)[R], T (&re)[R], T (&im)[R]) {
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int r0 = r % 3, hi = r - r0;
+    const vec2<T> p = pm[hi + (r0 + 3 - H) % 3], q = pn[hi + (6 - r0 - H) % 3];
+    if constexpr (SECOND) {
+      re[r] = fmaT(-p.x, q.y, fmaT(p.y, q.x, re[r]));
+      im[r] = fmaT(p.x, q.x, fmaT(p.y, q.y, im[r]));
+    } else {
+      re[r] = fmaT(p.x, q.x, p.y * q.y);
+      im[r] = fmaT(p.x, q.y, -(p.y * q.x));
+    }
+  }
+}
+
+template <typename T, int NT, int RT, int NL>
+__global__ __launch_bounds__(NT, ManaWaves<T>::row) void k_mana_rowfamilies(ManaFamilyArgs A) {
+  constexpr int R = pow3c(RT);
+  constexpr int ROWLEN = pow3c(NL);
+  constexpr int S0 = NL - RT;                // thread trits of the first layout (row trits 1 .. S0)
+  constexpr int TPR = pow3c(S0);             // threads per row
+  constexpr int G = mana_rows_per_tile(NT, TPR, true);
+  constexpr int LG = log3c(G);
+  static_assert(NL >= RT && G >= 1 && pow3c(LG) == G, "tile shape");
+  static_assert(S0 <= 5 && LG <= 5, "8-bit digit tables");
+  static_assert(RT >= 2, "a register trit beside the lowest");
+  constexpr int K = (NL + RT - 1) / RT;
+  static_assert(K <= 4, "at most four rounds");
+  constexpr int LDS_N = K > 1 ? G * ROWLEN : 1;
+  constexpr uint32_t VB = sizeof(vec2<T>);
+
+  __shared__ T lds[LDS_N];
+
+  const uint32_t tau = threadIdx.x;
+  const uint32_t g = tau / TPR;
+  const uint32_t tp = tau % TPR;
+  const bool tact = g < (uint32_t)G;
+  const __amdgpu_buffer_rsrc_t rs = buf_view(A.psi, A.psi_bytes);
+  const int64_t tile = xcd_tile(blockIdx.x, A.n_tiles);
+  const int64_t xb = tile / A.n_six;          // row block (uniform)
+  const uint32_t six = (uint32_t)(tile - xb * A.n_six);  // sextet of shifts (uniform)
+
+  uint32_t tm[S0 > 0 ? S0 : 1], tn[S0 > 0 ? S0 : 1], gm[LG > 0 ? LG : 1], gn[LG > 0 ? LG : 1];
+  {
+    uint32_t x = tp, p = 1;
+#pragma unroll
+    for (int i = 0; i < S0; ++i, p *= 3u, x /= 3u) {
+      tm[i] = trit_table(x % 3u, p, false);
+      tn[i] = trit_table(x % 3u, p, true);
+    }
+    x = g;
+    p = 1;
+#pragma unroll
+    for (int i = 0; i < LG; ++i, p *= 3u, x /= 3u) {
+      gm[i] = trit_table(x % 3u, p, false);
+      gn[i] = trit_table(x % 3u, p, true);
+    }
+  }
+
+  // The amplitudes of the family of shifts a, a + 1, a + 2 (a a multiple of 3): pm[r] = psi at x - a and
+  // pn[r] at -x - a, except that register trit 0 (the lowest) counts the source's trit itself.
+  vec2<T> pm[R], pn[R];
+  auto gather = [&](uint32_t a) {
+    const uint32_t ah = a / (uint32_t)ROWLEN, al = a % (uint32_t)ROWLEN;
+    // row part: xh = xb G + g, so (xh - ah) digit-wise = G (xb - ah / G) + (g - ah mod G)
+    uint32_t rqm = 0, rqn = 0;
+    {
+      uint32_t x = (uint32_t)xb, h = ah / (uint32_t)G, p = 1;
+      for (int i = 0; i < A.nhq; ++i, p *= 3u, x /= 3u, h /= 3u) {
+        const uint32_t xd = x % 3u, hd = h % 3u;
+        rqm += ((3u + xd - hd) % 3u) * p;
+        rqn += ((6u - xd - hd) % 3u) * p;
+      }
+    }
+    uint32_t rm = 0, rn = 0;
+    {
+      uint32_t h = ah;
+#pragma unroll
+      for (int i = 0; i < LG; ++i, h /= 3u) {
+        const uint32_t sh = 8u * (h % 3u);
+        rm += __builtin_amdgcn_ubfe(gm[i], sh, 8);
+        rn += __builtin_amdgcn_ubfe(gn[i], sh, 8);
+      }
+    }
+    uint32_t xm = 0, xn = 0, h = al / 3u;
+#pragma unroll
+    for (int i = 0; i < S0; ++i, h /= 3u) {
+      const uint32_t sh = 8u * (h % 3u);
+      xm += __builtin_amdgcn_ubfe(tm[i], sh, 8);
+      xn += __builtin_amdgcn_ubfe(tn[i], sh, 8);
+    }
+    const uint32_t vm = ((rqm * (uint32_t)G + rm) * (uint32_t)ROWLEN + 3u * xm) * VB;
+    const uint32_t vn = ((rqn * (uint32_t)G + rn) * (uint32_t)ROWLEN + 3u * xn) * VB;
+    uint32_t cm[RT - 1][3], cn[RT - 1][3], p = 3u * (uint32_t)TPR * VB;
+#pragma unroll
+    for (int i = 0; i < RT - 1; ++i, p *= 3u, h /= 3u) {
+      const uint32_t hd = h % 3u;
+#pragma unroll
+      for (uint32_t t = 0; t < 3; ++t) {
+        cm[i][t] = ((3u + t - hd) % 3u) * p;
+        cn[i][t] = ((6u - t - hd) % 3u) * p;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; r += 3) {
+      uint32_t om = 0, on = 0;
+#pragma unroll
+      for (int i = 0; i < RT - 1; ++i) {
+        const int t = (r / pow3c(i + 1)) % 3;
+        om += cm[i][t];
+        on += cn[i][t];
+      }
+      buf_ld3(&pm[r], rs, vm, om);
+      buf_ld3(&pn[r], rs, vn, on);
+    }
+  };
+
+  vec2<T> *ex = (vec2<T> *)A.exch;
+  const uint64_t a0 = A.a_base + 6 * (uint64_t)six;
+  auto there = [&](uint32_t i) { return a0 + i >= A.a_lo && a0 + i < A.a_end; };  // uniform
+  const uint32_t xh = (uint32_t)xb * (uint32_t)G + g;
+#pragma unroll 1
+  for (uint32_t k = 0; k < 3; ++k) {
+    T re[R], im[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) re[r] = im[r] = T(0);
+    if (tact) {
+      if (k == 0) {
+        gather((uint32_t)a0);
+        if (there(0)) mana_product<T, R, 0, false>(pm, pn, re, im);
+        if (there(1)) mana_product<T, R, 1, true>(pm, pn, re, im);
+      } else if (k == 1) {
+        if (there(2)) mana_product<T, R, 2, false>(pm, pn, re, im);
+        if (there(3)) {  // (if not, neither are the later ones)
+          gather((uint32_t)a0 + 3u);
+          mana_product<T, R, 0, true>(pm, pn, re, im);
+        }
+      } else {
+        if (there(4)) mana_product<T, R, 1, false>(pm, pn, re, im);
+        if (there(5)) mana_product<T, R, 2, true>(pm, pn, re, im);
+      }
+    }
+    if constexpr (K >= 1) f3_regs<T, RT, 0, mr_H(NL, RT, 0)>(re, im);
+    if constexpr (K >= 2) {
+      relayout3_split<T, RT, mr_S(NL, RT, 0), mr_S(NL, RT, 1), ROWLEN>(re, im, lds, g, tp, tact);
+      f3_regs<T, RT, 0, mr_H(NL, RT, 1)>(re, im);
+    }
+    if constexpr (K >= 3) {
+      relayout3_split<T, RT, mr_S(NL, RT, 1), mr_S(NL, RT, 2), ROWLEN>(re, im, lds, g, tp, tact);
+      f3_regs<T, RT, 0, mr_H(NL, RT, 2)>(re, im);
+    }
+    if constexpr (K >= 4) {
+      relayout3_split<T, RT, mr_S(NL, RT, 2), mr_S(NL, RT, 3), ROWLEN>(re, im, lds, g, tp, tact);
+      f3_regs<T, RT, 0, mr_H(NL, RT, 3)>(re, im);
+    }
+    // Final layout S = 0: register r holds position r + R * tp; stored at column r * TPR + tp (a fixed
+    // column permutation) so that consecutive threads write consecutive addresses.
+    if (tact) {
+      const uint32_t ob = ((3u * six + k) * A.nhr + xh) * ROWLEN + tp;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        vec2<T> v;
+        v.x = re[r];
+        v.y = im[r];
+        st32(ex, ob + (uint32_t)r * TPR, v);
+      }
+    }
+  }
+}
+
+// The same one pair (a, a + 1) at a time, every pair with its own gathers: for states so large that a launch
+// holds only a few pairs (a sextet would not fit the memory-side cache).
+struct ManaWriteArgs {
+  const void *psi;
+  uint32_t psi_bytes;  // 3^N values
+  int nhq;             // row-index trits above the tile's G rows (nh - log3 G)
+  uint32_t nhr;        // 3^nh rows per pair
+  int64_t n_pairs;     // pairs in this launch
+  uint64_t a0;         // first shift of pair 0
+  uint64_t a_end;      // shifts >= a_end are absent
+  void *exch;          // [n_pairs][3^nh][3^NL]
+  int64_t n_tiles;     // (3^nh / G) * n_pairs
 };
 
 template <typename T, int NT, int RT, int NL>
@@ -617,12 +824,13 @@ __global__ __launch_bounds__(256) void k_mana_total(const double *acc, int64_t n
 // Host side
 // ------------------------------------------------------------------------------------------------
 static constexpr int MANA_NT = 256;
-static constexpr int MANA_GRID = 2048;  // fixed grid: per-block accumulators live across launches
+static constexpr int MANA_GRID = 2048;  // fixed grid of the summing kernels: per-block accumulators live across launches
 
 struct ManaPlan {
   int N, dbl, path, nl, nh;
   int RT;   // register trits of the resident kernel (path 1) or of both two-pass kernels (path 2)
   int batch_pairs;
+  int families;  // 1: the row pass takes six shifts (three pairs) at a time (batch_pairs a multiple of 3)
   int lanes;  // two-pass batches alternate over this many streams (own exchange and accumulators)
 };
 
@@ -664,6 +872,11 @@ static int mana_plan(int N, int dbl, int64_t batch, int streams, ManaPlan *p) {
     int64_t b = batch > 0 ? (batch + 1) / 2 : (int64_t)((192ull << 20) / per_pair);
     if ((size_t)b * per_pair > (3ull << 30)) b = (int64_t)((3ull << 30) / per_pair);  // 32-bit offsets
     if (b < 1) b = 1;
+    // Shared gathers where the memory-side cache holds at least 12 pairs (n <= 13 complex64, 12 complex128):
+    // there whole sextets fill a launch.  Larger states run pair by pair (n = 14 complex64, 500 shifts:
+    // 6.2 ms against 6.4 with one sextet per launch; n = 15, 100 shifts: 4.5 against 5.1).
+    P.families = (192ull << 20) / per_pair >= 12;
+    if (P.families) b = b < 3 ? 3 : b - b % 3;
     P.batch_pairs = (int)b;
     P.lanes = streams ? streams : MANA_STREAMS_DEFAULT;
   }
@@ -710,7 +923,7 @@ static int launch_mana_resident(int NL, ManaRowArgs A, hipStream_t st) {
 }
 
 template <typename T, int RT, int NL>
-static int launch_mana_write_nl(ManaWriteArgs A, int nh, hipStream_t st) {
+static int launch_mana_pairs_nl(ManaWriteArgs A, int nh, hipStream_t st) {
   constexpr int G = mana_rows_per_tile(MANA_NT, pow3c(NL - RT), true);
   constexpr int LG = log3c(G);
   if (nh < LG) return fail(E_UNSUPPORTED, "mana: 3^%d rows per pair, fewer than one tile of %d rows", nh, G);
@@ -721,20 +934,40 @@ static int launch_mana_write_nl(ManaWriteArgs A, int nh, hipStream_t st) {
   return OK;
 }
 
-template <typename T, int RT>
-static int launch_mana_write(int NL, int nh, ManaWriteArgs A, hipStream_t st) {
-#define HM_MWR(nl) \
-  case nl:         \
-    return launch_mana_write_nl<T, RT, nl>(A, nh, st);
-  if constexpr (sizeof(T) == 4 && RT == 3) {
-    switch (NL) { HM_MWR(4) HM_MWR(5) HM_MWR(6) HM_MWR(7) HM_MWR(8) default: break; }
-  } else if constexpr (sizeof(T) == 8 && RT == 2) {
-    switch (NL) { HM_MWR(4) HM_MWR(5) HM_MWR(6) HM_MWR(7) default: break; }
-  } else if constexpr (sizeof(T) == 8 && RT == 3) {
-    switch (NL) { HM_MWR(8) default: break; }
+template <typename T>
+static int launch_mana_pairs(int RT, int NL, int nh, ManaWriteArgs A, hipStream_t st) {
+  if (RT == 3 && NL == 8) return launch_mana_pairs_nl<T, 3, 8>(A, nh, st);
+  if constexpr (sizeof(T) == 4) {
+    if (RT == 3 && NL == 7) return launch_mana_pairs_nl<T, 3, 7>(A, nh, st);
+  } else {
+    if (RT == 2 && NL == 7) return launch_mana_pairs_nl<T, 2, 7>(A, nh, st);
   }
-#undef HM_MWR
   return fail(E_UNSUPPORTED, "mana: no row-pass kernel for rows of 3^%d (RT %d)", NL, RT);
+}
+
+template <typename T, int NL>
+static int launch_mana_families_nl(ManaFamilyArgs A, int nh, hipStream_t st) {
+  constexpr int RT = 2;
+  constexpr int G = mana_rows_per_tile(MANA_NT, pow3c(NL - RT), true);
+  constexpr int LG = log3c(G);
+  if (nh < LG) return fail(E_UNSUPPORTED, "mana: 3^%d rows per pair, fewer than one tile of %d rows", nh, G);
+  A.nhq = nh - LG;
+  A.n_tiles = (int64_t)(A.nhr / (uint32_t)G) * A.n_six;
+  ProfScope prof("mana_rowpass_write", st);
+  hipLaunchKernelGGL((k_mana_rowfamilies<T, MANA_NT, RT, NL>), dim3((unsigned)A.n_tiles), dim3(MANA_NT), 0, st, A);
+  return OK;
+}
+
+template <typename T>
+static int launch_mana_families(int NL, int nh, ManaFamilyArgs A, hipStream_t st) {
+  switch (NL) {
+    case 4: return launch_mana_families_nl<T, 4>(A, nh, st);
+    case 5: return launch_mana_families_nl<T, 5>(A, nh, st);
+    case 6: return launch_mana_families_nl<T, 6>(A, nh, st);
+    case 7: return launch_mana_families_nl<T, 7>(A, nh, st);
+    default: break;
+  }
+  return fail(E_UNSUPPORTED, "mana: no family row-pass kernel for rows of 3^%d", NL);
 }
 
 template <typename T, int RT, int NH, int CT>
@@ -777,9 +1010,9 @@ static int mana_t(const ManaPlan &P, const void *psi, uint64_t a0, uint64_t a1, 
     const int64_t nz = (int64_t)(accb * (1 + P.lanes) / sizeof(double));
     hipLaunchKernelGGL(k_mana_zero, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, acc_row, nz);
   }
-  const int64_t n_pairs = (int64_t)((a1 - a0 + 1) / 2);
   int e = OK;
   if (P.path == 1) {
+    const int64_t n_pairs = (int64_t)((a1 - a0 + 1) / 2);
     ManaRowArgs A{};
     A.psi = psi;
     A.N = P.N;
@@ -806,6 +1039,10 @@ static int mana_t(const ManaPlan &P, const void *psi, uint64_t a0, uint64_t a1, 
   // buffer and column accumulators, so lanes share no memory they write.
   const size_t xb = align256((size_t)P.batch_pairs * (size_t)pow3c(P.N) * (P.dbl ? 16 : 8));
   char *exch0 = w + accb * (1 + P.lanes);
+  // With families, pairs are counted from the first multiple of 3 at or below a0, three to a sextet of
+  // shifts (two families of three); shifts outside [a0, a1) are zero.
+  const uint64_t a_base = P.families ? a0 - a0 % 3 : a0;
+  const int64_t n_pairs = P.families ? 3 * (int64_t)((a1 - a_base + 5) / 6) : (int64_t)((a1 - a0 + 1) / 2);
   const int64_t n_batches = (n_pairs + P.batch_pairs - 1) / P.batch_pairs;
   const int L = (P.lanes > 1 && n_batches > 1) ? 2 : 1;
   hipStream_t lst[2] = {st, st};
@@ -828,16 +1065,28 @@ static int mana_t(const ManaPlan &P, const void *psi, uint64_t a0, uint64_t a1, 
     const int64_t p0 = k * P.batch_pairs;
     const int64_t nb = (n_pairs - p0) < P.batch_pairs ? (n_pairs - p0) : P.batch_pairs;
     void *ex_l = exch0 + (size_t)l * xb;
-    ManaWriteArgs A{};
-    A.psi = psi;
-    A.psi_bytes = (uint32_t)((size_t)pow3c(P.N) * sizeof(vec2<T>));
-    A.nhr = (uint32_t)pow3c(P.nh);
-    A.n_pairs = nb;
-    A.a0 = a0 + 2 * (uint64_t)p0;
-    A.a_end = a1;
-    A.exch = ex_l;
-    if (P.RT == 3) e = launch_mana_write<T, 3>(P.nl, P.nh, A, lst[l]);
-    else e = launch_mana_write<T, 2>(P.nl, P.nh, A, lst[l]);
+    if (P.families) {
+      ManaFamilyArgs A{};
+      A.psi = psi;
+      A.psi_bytes = (uint32_t)((size_t)pow3c(P.N) * sizeof(vec2<T>));
+      A.nhr = (uint32_t)pow3c(P.nh);
+      A.n_six = nb / 3;
+      A.a_base = a_base + 2 * (uint64_t)p0;
+      A.a_lo = a0;
+      A.a_end = a1;
+      A.exch = ex_l;
+      e = launch_mana_families<T>(P.nl, P.nh, A, lst[l]);
+    } else {
+      ManaWriteArgs A{};
+      A.psi = psi;
+      A.psi_bytes = (uint32_t)((size_t)pow3c(P.N) * sizeof(vec2<T>));
+      A.nhr = (uint32_t)pow3c(P.nh);
+      A.n_pairs = nb;
+      A.a0 = a0 + 2 * (uint64_t)p0;
+      A.a_end = a1;
+      A.exch = ex_l;
+      e = launch_mana_pairs<T>(P.RT, P.nl, P.nh, A, lst[l]);
+    }
     if (e) break;
     ManaColArgs C{};
     C.exch = ex_l;
