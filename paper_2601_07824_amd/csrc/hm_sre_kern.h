@@ -76,6 +76,65 @@ struct RowShape {
   static constexpr size_t LDS_BYTES = (size_t)LDS_N * sizeof(Elem);
 };
 
+// The NL butterfly stages of a tile's rows, from the product step's layout: K rounds, round k holds tile bits
+// [S_k, S_k + RB) in registers; then the lane stages.
+template <typename T, int RB, int NL, bool WRITE, bool SPLIT, typename E>
+__device__ __forceinline__ void row_stages(T (&re)[1 << RB], T (&im)[1 << RB], E *lds, uint32_t tau) {
+  constexpr int R = 1 << RB;
+  constexpr int LB = row_lane_bits<T>(NL, RB, WRITE);
+  constexpr int K = RB == 0 ? 0 : (NL + RB - 1) / RB - (LB > 0 ? 1 : 0);
+  static_assert(K <= 4, "at most four rounds");
+  if constexpr (K >= 1) wht_regs<T, R, 0, rp_H(NL, RB, 0)>(re, im);
+  if constexpr (K >= 2) {
+    if constexpr (SPLIT) relayout_split<T, R, RB, rp_S(NL, RB, 0), rp_S(NL, RB, 1)>(re, im, lds, tau);
+    else relayout<T, R, RB, rp_S(NL, RB, 0), rp_S(NL, RB, 1)>(re, im, lds, tau);
+    wht_regs<T, R, 0, rp_H(NL, RB, 1)>(re, im);
+  }
+  if constexpr (K >= 3) {
+    if constexpr (SPLIT) relayout_split<T, R, RB, rp_S(NL, RB, 1), rp_S(NL, RB, 2)>(re, im, lds, tau);
+    else relayout<T, R, RB, rp_S(NL, RB, 1), rp_S(NL, RB, 2)>(re, im, lds, tau);
+    wht_regs<T, R, 0, rp_H(NL, RB, 2)>(re, im);
+  }
+  if constexpr (K >= 4) {
+    if constexpr (SPLIT) relayout_split<T, R, RB, rp_S(NL, RB, 2), rp_S(NL, RB, 3)>(re, im, lds, tau);
+    else relayout<T, R, RB, rp_S(NL, RB, 2), rp_S(NL, RB, 3)>(re, im, lds, tau);
+    wht_regs<T, R, 0, rp_H(NL, RB, 3)>(re, im);
+  }
+  if constexpr (LB > 0) wht_lanes<T, R, LB>(re, im, tau);
+}
+
+// Row rt to the exchange.  The final layout has S = 0: register r holds row position b = r | (tlo << RB).  It
+// is stored at column (r << S0) | tlo, or with 2^5-value FP32 tiles registers r, r + 1 at columns 2 c, 2 c + 1,
+// c = ((r / 2) << S0) | tlo (16-byte stores): a fixed permutation of the columns (the column pass only needs
+// each column to stay a column) in which consecutive lanes write consecutive addresses.
+template <typename T, int RB, int NL>
+__device__ __forceinline__ void row_store(vec2<T> *ex, uint32_t rt, uint32_t tlo, const T (&re)[1 << RB],
+                                          const T (&im)[1 << RB]) {
+  constexpr int R = 1 << RB, S0 = NL - RB;
+  if constexpr (sizeof(T) == 4 && RB == 5) {
+    float4 *ex4 = (float4 *)ex;
+    const uint32_t ob4 = (rt << (NL - 1)) | tlo;
+#pragma unroll
+    for (int r = 0; r < R; r += 2) {
+      float4 v;
+      v.x = re[r];
+      v.y = im[r];
+      v.z = re[r + 1];
+      v.w = im[r + 1];
+      st32(ex4, ob4 + ((uint32_t)(r >> 1) << S0), v);
+    }
+  } else {
+    const uint32_t ob = (rt << NL) | tlo;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      vec2<T> v;
+      v.x = re[r];
+      v.y = im[r];
+      st32(ex, ob + ((uint32_t)r << S0), v);
+    }
+  }
+}
+
 // Arguments of one state's workgroup-resident tiles inside a persistent launch: the fields of
 // RowPassArgs that a single-state, all-shifts, reducing row pass reads (no pointer table).
 struct StateTileArgs {
@@ -112,9 +171,6 @@ __device__ __forceinline__ void rowpass_tiles(const Args &A, int64_t t0, int64_t
   constexpr int TB = LT + RB;
   static_assert(TB >= NL && NL >= RB, "tile must hold whole rows");
   constexpr int S0 = NL - RB;
-  constexpr int LB = row_lane_bits<T>(NL, RB, WRITE);
-  constexpr int K = RB == 0 ? 0 : (NL + RB - 1) / RB - (LB > 0 ? 1 : 0);
-  static_assert(K <= 4, "at most four rounds");
   constexpr int SEG = 1 << S0;           // threads per row-task
   constexpr int G = 1 << (TB - NL);      // row-tasks per tile
   constexpr bool WAVE_UNIFORM = SEG >= 64;
@@ -153,57 +209,10 @@ __device__ __forceinline__ void rowpass_tiles(const Args &A, int64_t t0, int64_t
     T re[R], im[R];
     sre_product<T, RB, NL, (SPLIT || WRITE) ? 8 : R>(ps, half, a, ch, tlo, active, re, im);
 
-    // NL butterfly stages: K rounds, round k holds tile bits [S_k, S_k + RB) in registers; then the
-    // lane stages.
-    if constexpr (K >= 1) wht_regs<T, R, 0, rp_H(NL, RB, 0)>(re, im);
-    if constexpr (K >= 2) {
-      if constexpr (SPLIT) relayout_split<T, R, RB, rp_S(NL, RB, 0), rp_S(NL, RB, 1)>(re, im, lds, tau);
-      else relayout<T, R, RB, rp_S(NL, RB, 0), rp_S(NL, RB, 1)>(re, im, lds, tau);
-      wht_regs<T, R, 0, rp_H(NL, RB, 1)>(re, im);
-    }
-    if constexpr (K >= 3) {
-      if constexpr (SPLIT) relayout_split<T, R, RB, rp_S(NL, RB, 1), rp_S(NL, RB, 2)>(re, im, lds, tau);
-      else relayout<T, R, RB, rp_S(NL, RB, 1), rp_S(NL, RB, 2)>(re, im, lds, tau);
-      wht_regs<T, R, 0, rp_H(NL, RB, 2)>(re, im);
-    }
-    if constexpr (K >= 4) {
-      if constexpr (SPLIT) relayout_split<T, R, RB, rp_S(NL, RB, 2), rp_S(NL, RB, 3)>(re, im, lds, tau);
-      else relayout<T, R, RB, rp_S(NL, RB, 2), rp_S(NL, RB, 3)>(re, im, lds, tau);
-      wht_regs<T, R, 0, rp_H(NL, RB, 3)>(re, im);
-    }
-    if constexpr (LB > 0) wht_lanes<T, R, LB>(re, im, tau);
+    row_stages<T, RB, NL, WRITE, SPLIT>(re, im, lds, tau);
 
     if constexpr (WRITE) {
-      // Final layout has S = 0: register r holds row position b = r | (tlo << RB).  It is stored at
-      // column (r << S0) | tlo (a fixed permutation of the columns; the column pass only needs each
-      // column to stay a column), so consecutive lanes write consecutive addresses.
-      if (active) {
-        vec2<T> *ex = (vec2<T> *)A.exch;
-        if constexpr (sizeof(T) == 4 && RB == 5) {
-          // 16-byte stores: registers r, r + 1 of thread tlo go to columns 2 c, 2 c + 1 with
-          // c = ((r / 2) << S0) | tlo (another fixed column permutation)
-          float4 *ex4 = (float4 *)A.exch;
-          const uint32_t ob4 = ((uint32_t)rt << (NL - 1)) | tlo;
-#pragma unroll
-          for (int r = 0; r < R; r += 2) {
-            float4 v;
-            v.x = re[r];
-            v.y = im[r];
-            v.z = re[r + 1];
-            v.w = im[r + 1];
-            st32(ex4, ob4 + ((uint32_t)(r >> 1) << S0), v);
-          }
-        } else {
-          const uint32_t ob = ((uint32_t)rt << NL) | tlo;
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            vec2<T> v;
-            v.x = re[r];
-            v.y = im[r];
-            st32(ex, ob + ((uint32_t)r << S0), v);
-          }
-        }
-      }
+      if (active) row_store<T, RB, NL>((vec2<T> *)A.exch, (uint32_t)rt, tlo, re, im);
     } else {
       double *o = A.shift_sums + slot * A.nacc;
       double s0 = 0.0;
@@ -228,6 +237,89 @@ __global__ __launch_bounds__(NT, (WRITE ? TwoPassWaves<T, SPLIT>::value : 1)) vo
   __shared__ typename Sh::Elem lds[Sh::LDS_N];
   __shared__ double red[NT / 64 + 1];
   rowpass_tiles<T, NT, RB, NL, WRITE, QM, SPLIT, RowPassArgs, true>(A, A.tile0 + blockIdx.x, gridDim.x, lds, red);
+}
+
+// Row pass of 2^GB consecutive shifts per workgroup.  For shifts that agree above their low GB bits (and
+// are at least 2^GB, so the top set bit too) the gathers of a row are the same values: psi_x is the
+// same, and psi_{x^a} moves within aligned groups of 2^GB row positions, which sit in 2^GB lanes.  So a
+// thread gathers its psi_x and psi_{x^a} once and, from one shift to the next, exchanges the latter
+// across the lanes (one DPP move per register word; the low bits of the shift run through a Gray code
+// of the moves' lane masks 1, 2, 7), instead of 16 B of gathers per folded FP32 value, which the L2 serves
+// at about 28 B per CU and clock.
+struct RowGroupArgs {
+  const void *psi;
+  int nf, nh;
+  int64_t n_slots;   // slot s holds shift a0 + s
+  uint64_t a0;       // at least 2^GB
+  void *exch;        // [n_slots][2^nh][2^NL]
+};
+// Bits of a group: 8 FP32 or 4 FP64 shifts (a launch of 2^25 FP32 values is then 1024 workgroups of 128
+// threads; 16 shifts leave half the chip idle, 4 gather twice as much: n = 18 87.0 us per row + column launch
+// pair with 8, 91.0 with 4, 92.2 with gathers for every shift; complex128 n = 17 48.7 with 4, 53.4 with 8, 56.9).
+template <typename T>
+constexpr int row_group_bits(int NL, int RB) {
+  const int most = sizeof(T) == 4 ? 3 : 2;
+  return NL - RB < most ? NL - RB : most;
+}
+
+// Two waves per SIMD: the two gathered arrays and the values are 192 registers (96 for FP32 tiles of 2^4
+// values: four waves).
+template <typename T, int NT, int RB, int NL, bool SPLIT>
+__global__ __launch_bounds__(NT, (sizeof(T) == 4 && RB == 4 ? 4 : 2)) void k_sre_rowgroup(RowGroupArgs A) {
+  using Sh = RowShape<T, NT, RB, NL, SPLIT>;
+  __shared__ typename Sh::Elem lds[Sh::LDS_N];
+  constexpr int R = 1 << RB;
+  constexpr int TB = ilog2c(NT) + RB;
+  constexpr int S0 = NL - RB, SEG = 1 << S0;
+  constexpr int LG = TB - NL;  // 2^LG rows per tile
+  constexpr int GB = row_group_bits<T>(NL, RB);
+  constexpr uint32_t VB = sizeof(vec2<T>);
+  const uint32_t tau = threadIdx.x;
+  const uint32_t tlo = tau & (SEG - 1);
+  const uint32_t rb = (uint32_t)blockIdx.x & ((1u << (A.nh - LG)) - 1u);
+  const uint32_t grp = (uint32_t)blockIdx.x >> (A.nh - LG);
+  const uint32_t a_lo = (uint32_t)A.a0, a_hi = a_lo + (uint32_t)A.n_slots;  // shifts [a_lo, a_hi)
+  const uint32_t ag = (a_lo & ~((1u << GB) - 1u)) + (grp << GB);
+  const uint32_t ch = (rb << LG) + (tau >> S0);
+  // bit j >= GB of the index is inserted into the row index, the register bits or the thread bits (as
+  // in sre_product)
+  const int j = 31 - __builtin_clz(ag);
+  const uint32_t xr = j >= NL ? ins0_32(ch, j - NL) : ch << 1;
+  const uint32_t yr = j >= NL ? xr ^ (ag >> NL) : xr;
+  const uint32_t xt = j >= S0 ? tlo : ins0_32(tlo, j);
+  const uint32_t yt = xt ^ (ag & (uint32_t)(SEG - 1));
+  const int jj = j < S0 ? 0 : j >= NL ? RB : j - S0;
+  const uint32_t lomask = (1u << jj) - 1u, amid = (ag >> S0) & (uint32_t)(R - 1);
+  const uint32_t vx = ((xr << NL) + xt) * VB, vy = ((yr << NL) + yt) * VB;
+  const __amdgpu_buffer_rsrc_t rs = buf_view(A.psi, (2u << A.nf) * VB);
+  vec2<T> px[R], py[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t e = 2u * (uint32_t)r - ((uint32_t)r & lomask);  // ins0(r, jj)
+    px[r] = buf_ld((vec2<T> *)nullptr, rs, vx, (e << S0) * VB);
+    py[r] = buf_ld((vec2<T> *)nullptr, rs, vy, ((e ^ amid) << S0) * VB);
+  }
+  uint32_t lo = 0;
+#pragma unroll 1
+  for (uint32_t i = 0; i < (1u << GB); ++i) {
+    if (i & 1u) {
+      lane_move_all<T, R, 0xB1>(py);  // lane mask 1 (quad_perm 1,0,3,2)
+      lo ^= 1u;
+    } else if (i & 2u) {
+      lane_move_all<T, R, 0x4E>(py);  // 2 (quad_perm 2,3,0,1)
+      lo ^= 2u;
+    } else if (i) {
+      lane_move_all<T, R, 0x141>(py);  // 7 (row_half_mirror)
+      lo ^= 7u;
+    }
+    const uint32_t a = ag | lo;
+    if (a < a_lo || a >= a_hi) continue;  // uniform
+    T re[R], im[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) cmul_conj<T>(py[r], px[r], re[r], im[r]);
+    row_stages<T, RB, NL, true, SPLIT>(re, im, lds, tau);
+    row_store<T, RB, NL>((vec2<T> *)A.exch, ((a - a_lo) << A.nh) + ch, tlo, re, im);
+  }
 }
 
 // The same with a register budget for at least MINW waves per SIMD (resident tiles of <= 2^13
@@ -587,6 +679,56 @@ static int launch_rowwrite(int rb, int NL, RowPassArgs A, bool split, hipStream_
   return fail(E_UNSUPPORTED, "row pass: register tile 2^%d (split %d) not built for this dtype", rb, (int)split);
 }
 
+// Consecutive shifts: the row pass by groups of shifts (k_sre_rowgroup) for rows of 2^8..2^13 values (FP32 tiles
+// of 2^4 values per thread, the gradient's: 2^8..2^10); the shifts below one group, among them a = 0, run one
+// by one.  Returns false where it does not apply (fewer rows per shift than a tile holds).
+template <typename T, int RB, int NL, int NT>
+static bool launch_rowgroup_nl(const RowPassArgs &A, int64_t skip, hipStream_t st) {
+  constexpr int LG = ilog2c(NT) + RB - NL, GB = row_group_bits<T>(NL, RB);
+  if (A.nh < LG) return false;
+  RowGroupArgs B{};
+  B.psi = A.psi;
+  B.nf = A.nf;
+  B.nh = A.nh;
+  B.n_slots = A.n_slots - skip;
+  B.a0 = A.a0 + (uint64_t)skip;
+  B.exch = (vec2<T> *)A.exch + (skip << A.nf);
+  const int64_t groups = (int64_t)(((B.a0 + (uint64_t)B.n_slots - 1) >> GB) - (B.a0 >> GB) + 1);
+  ProfScope prof("sre_rowpass_write", st);
+  hipLaunchKernelGGL((k_sre_rowgroup<T, NT, RB, NL, true>), dim3((unsigned)(groups << (A.nh - LG))), dim3(NT), 0, st, B);
+  return true;
+}
+template <typename T>
+static bool launch_rowgroup(int rb, int NL, const RowPassArgs &A, int64_t skip, hipStream_t st) {
+#define HM_RG(RB, nl, nt)   case nl: return launch_rowgroup_nl<T, RB, nl, nt>(A, skip, st);
+  if constexpr (sizeof(T) == 4) {
+    if (rb == 5) switch (NL) {
+        HM_RG(5, 8, 128) HM_RG(5, 9, 128) HM_RG(5, 10, 128) HM_RG(5, 11, 128) HM_RG(5, 12, 128) HM_RG(5, 13, 256)
+        default: break;
+      }
+    if (rb == 4) switch (NL) { HM_RG(4, 8, 256) HM_RG(4, 9, 256) HM_RG(4, 10, 256) default: break; }
+  } else {
+    if (rb == 4) switch (NL) {
+        HM_RG(4, 8, 128) HM_RG(4, 9, 128) HM_RG(4, 10, 128) HM_RG(4, 11, 128) HM_RG(4, 12, 256) HM_RG(4, 13, 512)
+        default: break;
+      }
+  }
+#undef HM_RG
+  return false;
+}
+template <typename T>
+static int launch_rows(int rb, int NL, RowPassArgs A, bool split, hipStream_t st) {
+  if (!A.rows && NL >= 8) {
+    const uint64_t first = 1ull << row_group_bits<T>(NL, rb);
+    int64_t skip = A.a0 < first ? (int64_t)(first - A.a0) : 0;
+    if (skip < A.n_slots && launch_rowgroup<T>(rb, NL, A, skip, st)) {
+      if (skip == 0) return OK;
+      A.n_slots = skip;  // the rest is per shift
+    }
+  }
+  return launch_rowwrite<T>(rb, NL, A, split, st);
+}
+
 template <typename T, int NT, int RB, int NH, bool SPLIT>
 static void launch_col_nh(ColPassArgs A, int qm, hipStream_t st) {
   constexpr int CB = ilog2c(NT) + RB - NH;
@@ -696,9 +838,11 @@ int shift_sums_t(const SrePlan &p, const void *psi, const QArgs &qa, uint64_t a0
       return fail(E_HIP, "SRE: stream fork failed");
   }
   int64_t bi = 0;
-  for (int64_t s0 = 0; s0 < n_slots; s0 += p.batch, ++bi) {
+  for (int64_t s0 = 0, nb = 0; s0 < n_slots; s0 += nb, ++bi) {
     Lane &ln = lane[bi % L];
-    const int64_t nb = (n_slots - s0) < p.batch ? (n_slots - s0) : p.batch;
+    // a first batch that ends at a whole group of shifts (launch_rows) where consecutive shifts start inside one
+    const int64_t off = !rows && p.batch >= 64 ? (int64_t)((a0 + (uint64_t)s0) & 7u) : 0;
+    nb = (n_slots - s0) < p.batch - off ? (n_slots - s0) : p.batch - off;
     RowPassArgs A{};
     A.psi = psi;
     A.nf = p.nf;
@@ -709,7 +853,7 @@ int shift_sums_t(const SrePlan &p, const void *psi, const QArgs &qa, uint64_t a0
     A.exch = ln.exch;
     A.nacc = nacc;
     A.qa = qa;
-    int e = launch_rowwrite<T>(p.row_rb, p.nl, A, p.split != 0, ln.st);
+    int e = launch_rows<T>(p.row_rb, p.nl, A, p.split != 0, ln.st);
     if (e) return e;
     ColPassArgs C{};
     C.exch = ln.exch;

@@ -126,6 +126,14 @@ __device__ __forceinline__ double lane_move(double x) {
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 template <typename T, int R, int CTRL>
+__device__ __forceinline__ void lane_move_all(vec2<T> (&v)[R]) {
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    v[r].x = lane_move<CTRL>(v[r].x);
+    v[r].y = lane_move<CTRL>(v[r].y);
+  }
+}
+template <typename T, int R, int CTRL>
 __device__ __forceinline__ void lane_stage(T (&re)[R], T (&im)[R], T s) {
 #pragma unroll
   for (int r = 0; r < R; ++r) re[r] = fmaT(lane_move<CTRL>(re[r]), s, re[r]);
