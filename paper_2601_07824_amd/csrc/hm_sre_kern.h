@@ -50,6 +50,8 @@ struct RowPassArgs {
   int64_t n_tiles;
   int64_t tile0;        // first tile of this launch (launches of one workgroup per tile, in chunks)
   QArgs qa;
+  // two-pass rows only: tiles run through the shifts of one row block before the next row block
+  int by_rows;
   // batched mode (n_states > 0): slot s is shift s mod 2^state_bits of state s >> state_bits
   int n_states;
   int state_bits;
@@ -149,6 +151,7 @@ struct StateTileArgs {
   int nacc;
   int64_t n_tiles;
   const QArgs &qa;  // the launch's Renyi indices (kernel argument), not copied
+  static constexpr int by_rows = 0;
   static constexpr int n_states = 0;
   static constexpr int state_bits = 0;
   static constexpr const void *psis[1] = {nullptr};
@@ -181,7 +184,14 @@ __device__ __forceinline__ void rowpass_tiles(const Args &A, int64_t t0, int64_t
   const uint32_t half = 1u << A.nf;
 
   for (int64_t tile = t0; tile < A.n_tiles; tile += tstep) {
-    const int64_t rt = tile * G + g;
+    int64_t rt = tile * G + g;
+    if constexpr (WRITE) {
+      if (A.by_rows) {  // (n_slots 2^nh / G tiles) tile -> row block t / n_slots of shift t mod n_slots
+        const uint32_t t = (uint32_t)xcd_tile(tile, A.n_tiles), ns = (uint32_t)A.n_slots;
+        const uint32_t blk = t / ns;
+        rt = ((int64_t)(t - blk * ns) << A.nh) + (int64_t)blk * G + g;
+      }
+    }
     const int64_t slot = rt >> A.nh;
     const uint64_t ch = (uint64_t)rt & ((1ull << A.nh) - 1ull);
     const bool active = slot < A.n_slots;
@@ -225,14 +235,14 @@ __device__ __forceinline__ void rowpass_tiles(const Args &A, int64_t t0, int64_t
   }
 }
 
-// Split-staged FP32 row-pass tiles keep to a register budget of four waves per SIMD (the column
-// pass would spill under it).
-template <typename T, bool SPLIT>
-struct TwoPassWaves { static constexpr int value = (SPLIT && sizeof(T) == 4) ? 4 : 1; };
+// Split-staged FP32 row-pass tiles keep to a register budget of four waves per SIMD, rows of 2^10 values, which
+// would spill, of three (2048 listed shifts at N = 20: 4.13 -> 3.77 ms; the column pass would spill under four).
+template <typename T, bool SPLIT, int NL>
+struct TwoPassWaves { static constexpr int value = (SPLIT && sizeof(T) == 4) ? (NL == 10 ? 3 : 4) : 1; };
 
 // One workgroup per tile (grid = n_tiles).
 template <typename T, int NT, int RB, int NL, bool WRITE, int QM, bool SPLIT = false>
-__global__ __launch_bounds__(NT, (WRITE ? TwoPassWaves<T, SPLIT>::value : 1)) void k_sre_rowpass(RowPassArgs A) {
+__global__ __launch_bounds__(NT, (WRITE ? TwoPassWaves<T, SPLIT, NL>::value : 1)) void k_sre_rowpass(RowPassArgs A) {
   using Sh = RowShape<T, NT, RB, NL, SPLIT>;
   __shared__ typename Sh::Elem lds[Sh::LDS_N];
   __shared__ double red[NT / 64 + 1];
@@ -637,9 +647,15 @@ static int launch_resident(int NL, RowPassArgs A, int qm, hipStream_t st, bool s
 template <typename T, int RB, bool SPLIT>
 static int launch_rowwrite_rb(int NL, RowPassArgs A, hipStream_t st) {
   constexpr int NT12 = 1 << (12 - RB), NT13 = 1 << (13 - RB), NT14 = 1 << (14 - RB), NT15 = 1 << (15 - RB);
+  // An explicit list has shifts of any distance: with the tiles in shift order every shift streams the whole
+  // state twice through the L2s.  Row block by row block (each XCD a contiguous share, so a row block of psi_x
+  // stays in its L2 for all the launch's shifts that fold on the same bit) only psi_{x^a} is streamed.  From
+  // 2^18 folded values on, where the state outgrows an L2 (2048 rows, complex64 N = 22 20.5 -> 18.4 ms,
+  // complex128 N = 20 10.0 -> 8.8 ms).
 #define HM_RW(nl, nt)                                               \
   case nl:                                                          \
     A.n_tiles = row_tiles<nt, RB, nl>(A);                           \
+    A.by_rows = A.rows && A.nf >= 18 && (nl) + A.nh >= ilog2c(nt) + RB; \
     launch_row_q<T, nt, RB, nl, true, SPLIT>(A, false, st);         \
     return OK;
   switch (NL) {
@@ -650,6 +666,7 @@ static int launch_rowwrite_rb(int NL, RowPassArgs A, hipStream_t st) {
     case 14:
       if constexpr (sizeof(T) == 4 && NT14 <= 1024) {
         A.n_tiles = row_tiles<NT14, RB, 14>(A);
+        A.by_rows = A.rows != nullptr;
         launch_row_q<T, NT14, RB, 14, true, SPLIT>(A, false, st);
         return OK;
       }
@@ -657,6 +674,7 @@ static int launch_rowwrite_rb(int NL, RowPassArgs A, hipStream_t st) {
     case 15:  // split staging only: whole-complex staging needs more registers than 1024 threads have
       if constexpr (sizeof(T) == 4 && NT15 <= 1024 && SPLIT) {
         A.n_tiles = row_tiles<NT15, RB, 15>(A);
+        A.by_rows = A.rows != nullptr;
         launch_row_q<T, NT15, RB, 15, true, SPLIT>(A, false, st);
         return OK;
       }
@@ -706,10 +724,10 @@ static bool launch_rowgroup(int rb, int NL, const RowPassArgs &A, int64_t skip, 
         HM_RG(5, 8, 128) HM_RG(5, 9, 128) HM_RG(5, 10, 128) HM_RG(5, 11, 128) HM_RG(5, 12, 128) HM_RG(5, 13, 256)
         default: break;
       }
-    if (rb == 4) switch (NL) { HM_RG(4, 8, 256) HM_RG(4, 9, 256) HM_RG(4, 10, 256) default: break; }
+    if (rb == 4) switch (NL) { HM_RG(4, 7, 256) HM_RG(4, 8, 256) HM_RG(4, 9, 256) HM_RG(4, 10, 256) default: break; }
   } else {
     if (rb == 4) switch (NL) {
-        HM_RG(4, 8, 128) HM_RG(4, 9, 128) HM_RG(4, 10, 128) HM_RG(4, 11, 128) HM_RG(4, 12, 256) HM_RG(4, 13, 512)
+        HM_RG(4, 7, 128) HM_RG(4, 8, 128) HM_RG(4, 9, 128) HM_RG(4, 10, 128) HM_RG(4, 11, 128) HM_RG(4, 12, 256) HM_RG(4, 13, 512)
         default: break;
       }
   }
@@ -718,7 +736,7 @@ static bool launch_rowgroup(int rb, int NL, const RowPassArgs &A, int64_t skip, 
 }
 template <typename T>
 static int launch_rows(int rb, int NL, RowPassArgs A, bool split, hipStream_t st) {
-  if (!A.rows && NL >= 8) {
+  if (!A.rows && NL >= 7) {
     const uint64_t first = 1ull << row_group_bits<T>(NL, rb);
     int64_t skip = A.a0 < first ? (int64_t)(first - A.a0) : 0;
     if (skip < A.n_slots && launch_rowgroup<T>(rb, NL, A, skip, st)) {
