@@ -330,9 +330,18 @@ __device__ __forceinline__ T sum_kind(T (&re)[R], T (&im)[R], QKind kind, double
     case Q_FOUR: each_real(re, im, [&](T x) { const T t = x * x, t2 = t * t; a += t2 * t2; }); break;
     default:
       if constexpr (POW) {
-        each_real_rotating<T, R, 1, 1>(re, im, [&](T x) {
+        // FP64: no branch around pow, so that the two chains of a pass step overlap (8 indices, N = 14:
+        // 40.4 -> 13.0 ms; N = 8 134 -> 122 us); FP32 keeps it (33.1 against 35.3 ms at N = 15).
+        constexpr int C = sizeof(T) == 4 ? 8 : 4;
+        each_real_rotating<T, R, (R < C ? R : C), 1>(re, im, [&](T x) {
           const T t = x * x;
-          a += t > T(0) ? (T)pow(t, (T)q) : T(0);
+          if constexpr (sizeof(T) == 8) {
+            T v = pow(t, (T)q);
+            asm volatile("" : "+v"(v));
+            a += t > T(0) ? v : T(0);
+          } else {
+            a += t > T(0) ? (T)pow(t, (T)q) : T(0);
+          }
         });
       }
       break;
@@ -345,6 +354,9 @@ __device__ __forceinline__ T sum_kind(T (&re)[R], T (&im)[R], QKind kind, double
 // every q is 1, 2, 3 or 4 (pow's temporaries would not fit beside the values of the largest tiles);
 // QM == 0: any q.  Measured for q = (1, 2, 3) on MI355X against all kinds unrolled with one accumulator
 // per q: complex64 N = 13 142 -> 78 us, N = 16 11.3 -> 6.3 ms; complex128 N = 15 15.6 -> 10.5 ms.
+// Eight other indices: complex128 N = 8 163 -> 122 us, N = 14 22.5 -> 13.1 ms; complex64 N = 8 204 -> 189 us,
+// N = 13 and 14 as before, N = 15 25.8 -> 33.0 ms (its registers leave room for one workgroup per CU, not two;
+// held to the budget of two they spill and it takes the same 33 ms).
 template <typename T, int R, int NT, int SEG, int QM, typename F>
 __device__ __forceinline__ void tile_sums(T (&re)[R], T (&im)[R], const QArgs &qa, double *red, uint32_t tau, F out) {
   if constexpr (QM == 2) {
