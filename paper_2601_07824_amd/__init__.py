@@ -164,9 +164,9 @@ def default_context() -> Context:
 # ------------------------------------------------------------------------------------------------
 # marshalling helpers (torch is used only for memory and streams)
 # ------------------------------------------------------------------------------------------------
-# A small call costs what these helpers cost (about 14 us for hm_sre at n = 8 with two launches, before 10 us):
-# the module is looked up once, pointers and streams are passed as the integers that ctypes takes for void *,
-# and the qubit count comes from the length's bits.
+# Small calls are bound by their launches and by these helpers (sre at n <= 7: about 9 us a call, of which the
+# kernel is 8.9): the module is looked up once, pointers and streams are passed as the integers that ctypes takes for void *
+# (the current stream's raw handle 0.3 us, its Stream object 2.7), and the qubit count comes from the length's bits.
 _torch_module = None
 
 
@@ -206,7 +206,11 @@ def _state(psi, d: int):
 
 
 def _stream(stream=None) -> int:
-    return (stream if stream is not None else _torch().cuda.current_stream()).cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    cuda = _torch().cuda
+    raw = getattr(_torch()._C, "_cuda_getCurrentRawStream", None)  # the handle without a Stream object around it
+    return raw(cuda.current_device()) if raw else cuda.current_stream().cuda_stream
 
 
 @functools.lru_cache(maxsize=256)

@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "hm_sre_kern.h"
+#include "hm_totals.h"
 
 namespace hm {
 
@@ -129,36 +130,15 @@ __global__ __launch_bounds__(NT) void k_sre_batch_persistent(BatchArgs B) {
 
 // One workgroup per state: fixed-order sum of its per-shift sums, finalised into
 // out[orig (nq + 1) ...] = {M_q..., lost_norm}.
-__global__ __launch_bounds__(256) void k_batch_totals(const BatchTab *tab, const double *shift_sums, int nacc, QArgs qa,
-                                                      double *out) {
-  __shared__ double red[256];
+static constexpr int BATCH_TOT_NT = 1024;
+__global__ __launch_bounds__(BATCH_TOT_NT) void k_batch_totals(const BatchTab *tab, const double *shift_sums, int nacc,
+                                                               QArgs qa, double *out) {
+  __shared__ double red[(HM_MAX_Q + 1) * BATCH_TOT_NT / 64];
   __shared__ double tot[HM_MAX_Q + 1];
   const BatchTab e = tab[blockIdx.x];
-  const uint32_t t = threadIdx.x;
   const int N = e.nf + 1;
-  const int64_t ns = (int64_t)1 << N;
-  const double *base = shift_sums + e.slot_base * nacc;
-  for (int k = 0; k < nacc; ++k) {
-    double s = 0.0;
-    for (int64_t i = t; i < ns; i += 256) s += base[i * nacc + k];
-    red[t] = s;
-    __syncthreads();
-    for (uint32_t w = 128; w > 0; w >>= 1) {
-      if (t < w) red[t] += red[t + w];
-      __syncthreads();
-    }
-    if (t == 0) tot[k] = red[0];
-    __syncthreads();
-  }
-  if (t == 0) {
-    double *o = out + (size_t)e.orig * (qa.nq + 1);
-    const double D = ldexp(1.0, N);
-    for (int i = 0; i < qa.nq; ++i) {
-      const double q = qa.q[i];
-      o[i] = (q == 1.0) ? -tot[1 + i] / D : log2(tot[1 + i] / D) / (1.0 - q);  // Eq. sre; q -> 1 limit
-    }
-    o[qa.nq] = 1.0 - tot[0] / D;
-  }
+  block_rows_sum<BATCH_TOT_NT>(shift_sums + e.slot_base * nacc, (int64_t)1 << N, nacc, red, tot);
+  sre_finalize_into(tot, N, qa, out + (size_t)e.orig * (qa.nq + 1));
 }
 
 __global__ void k_batch_zero_counter(unsigned long long *c) { *c = 0ull; }
@@ -266,7 +246,7 @@ int batch_persistent_run(int dbl, const void *const *psis, const int *ns, const 
   }
   if (e) return e;
   ProfScope prof("sre_batch_totals", st);
-  hipLaunchKernelGGL(k_batch_totals, dim3((unsigned)cnt), dim3(256), 0, st, (const BatchTab *)dtab, (const double *)ss,
+  hipLaunchKernelGGL(k_batch_totals, dim3((unsigned)cnt), dim3(BATCH_TOT_NT), 0, st, (const BatchTab *)dtab, (const double *)ss,
                      qa.nq + 1, qa, out);
   return hipPeekAtLastError() == hipSuccess ? OK : fail(E_HIP, "batched launch: %s", hipGetErrorString(hipGetLastError()));
 }

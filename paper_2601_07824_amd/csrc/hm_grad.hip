@@ -23,6 +23,7 @@
 #include "hm_internal.h"
 #include "hm_sre_dev.h"
 #include "hm_tile.h"
+#include "hm_totals.h"
 
 namespace hm {
 
@@ -199,50 +200,46 @@ __global__ __launch_bounds__((1 << (NL - RB)) < 64 ? 64 : (1 << (NL - RB))) void
   }
 }
 
-// totals over blocks -> out = {M_q, lost_norm}; scale = 2 / ((1 - q) S_q ln 2) for the gradient.
-// Workgroup s handles state s: spart[s][nblk][2] -> out[2 s .. 2 s + 1], scale[s].  Fixed order:
-// thread t sums entries t, t + TOT_T, ... in turn, then a tree over the threads.
+// Sum of n pairs {sum |chi|^2, sum |chi|^{2q}} by a workgroup of NT threads -> {M_q, lost_norm} (out, if
+// given) and the gradient's factor 2 / ((1 - q) S_q ln 2).  Fixed order: thread t sums entries t, t + NT, ...
+// in turn, then a tree over the threads.
+template <int NT>
+__device__ __forceinline__ double grad_scale(const double2 *sp, int n, int N, double q, double *out, double *red,
+                                             double *tot) {
+  double s[2] = {0.0, 0.0};
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n; i += NT) {
+    const double2 v = sp[i];
+    s[0] += v.x;
+    s[1] += v.y;
+  }
+  block_sums<NT, 2>(s, 2, red, tot);
+  if (out && threadIdx.x == 0) {
+    const double D = ldexp(1.0, N);
+    out[0] = log2(tot[1] / D) / (1.0 - q);
+    out[1] = 1.0 - tot[0] / D;
+  }
+  return 2.0 / ((1.0 - q) * tot[1] * log(2.0));
+}
 static constexpr int TOT_T = 1024;
 __global__ __launch_bounds__(TOT_T) void k_grad_totals(const double *spart, int nblk, int N, double q, double *out,
                                                       double *scale) {
-  __shared__ double r1[TOT_T], rq[TOT_T];
-  const uint32_t t = threadIdx.x;
-  const double2 *sp = (const double2 *)spart + (size_t)blockIdx.x * nblk;
-  out += 2 * blockIdx.x;
-  scale += blockIdx.x;
-  double a = 0.0, b = 0.0;
-#pragma unroll 4
-  for (int i = t; i < nblk; i += TOT_T) {
-    const double2 v = sp[i];
-    a += v.x;
-    b += v.y;
-  }
-  r1[t] = a;
-  rq[t] = b;
-  __syncthreads();
-  for (uint32_t w = TOT_T / 2; w > 0; w >>= 1) {
-    if (t < w) {
-      r1[t] += r1[t + w];
-      rq[t] += rq[t + w];
-    }
-    __syncthreads();
-  }
-  if (t == 0) {
-    const double D = ldexp(1.0, N);
-    out[0] = log2(rq[0] / D) / (1.0 - q);
-    out[1] = 1.0 - r1[0] / D;
-    scale[0] = 2.0 / ((1.0 - q) * rq[0] * log(2.0));
-  }
+  __shared__ double red[2 * TOT_T / 64], tot[2];
+  const double f = grad_scale<TOT_T>((const double2 *)spart, nblk, N, q, out, red, tot);
+  if (threadIdx.x == 0) scale[0] = f;
 }
 
-// grad_s[y] = scale[s] * sum over blocks of G partials (fixed order); blockIdx.y = state s.
+// grad_s[y] = scale_s * sum over blocks of G partials (fixed order); blockIdx.y = state s.
 // A workgroup takes 64 consecutive y (one per lane, coalesced) x 16 groups of partials (one per
-// wave): wave k sums partials k, k + 16, ... in turn, then wave 0 adds the 16 group sums in order.
+// wave): wave k sums partials k, k + 16, ... in turn, then wave 0 adds the 16 group sums in order.  Every
+// workgroup also sums the state's at most 256 pairs of spart itself (a launch of its own for that took
+// 4.7 us); the first one of a state writes out[2 s .. 2 s + 1].
 static constexpr int RED_Y = 64, RED_G = 16;
 template <typename T>
-__global__ __launch_bounds__(RED_Y *RED_G) void k_grad_reduce(const vec2<T> *gpart, int nblk, int64_t n,
-                                                              const double *scale, GradOuts outs) {
+__global__ __launch_bounds__(RED_Y *RED_G) void k_grad_reduce(const vec2<T> *gpart, const double *spart, int nblk, int64_t n,
+                                                              int N, double q, double *out, GradOuts outs) {
   __shared__ double sr[RED_G][RED_Y], si[RED_G][RED_Y];
+  __shared__ double red[2 * RED_G], tot[2];
   const uint32_t ly = threadIdx.x % RED_Y, g = threadIdx.x / RED_Y;
   const int64_t y = (int64_t)blockIdx.x * RED_Y + ly;
   gpart += (size_t)blockIdx.y * nblk * n;
@@ -256,7 +253,8 @@ __global__ __launch_bounds__(RED_Y *RED_G) void k_grad_reduce(const vec2<T> *gpa
   }
   sr[g][ly] = gr;
   si[g][ly] = gi;
-  __syncthreads();
+  const double sc = grad_scale<RED_Y * RED_G>((const double2 *)spart + (size_t)blockIdx.y * nblk, nblk, N, q,
+                                              blockIdx.x == 0 ? out + 2 * blockIdx.y : nullptr, red, tot);  // (barriers inside)
   if (g == 0 && y < n) {
     double tr = 0.0, ti = 0.0;
 #pragma unroll
@@ -264,7 +262,6 @@ __global__ __launch_bounds__(RED_Y *RED_G) void k_grad_reduce(const vec2<T> *gpa
       tr += sr[k][ly];
       ti += si[k][ly];
     }
-    const double sc = scale[blockIdx.y];
     vec2<T> o;
     o.x = (T)(sc * tr);
     o.y = (T)(sc * ti);
@@ -290,8 +287,7 @@ static int grad_chunk(int batch) { return batch < HM_BATCH_PTRS ? batch : HM_BAT
 
 static size_t grad1_workspace(int N, int dbl, int states) {
   const size_t nb = (size_t)grad_blocks(N, states) * states;
-  return align256(nb * ((size_t)1 << N) * (dbl ? 16 : 8)) + align256(nb * 2 * sizeof(double)) +
-         align256((size_t)states * sizeof(double));
+  return align256(nb * ((size_t)1 << N) * (dbl ? 16 : 8)) + align256(nb * 2 * sizeof(double));
 }
 
 // Two-pass plan of the gradient: default split and tiles, sequential launches.
@@ -381,7 +377,6 @@ static int grad_t(int N, const void *const *psis, int states, double q, double *
   A.q = q;
   A.gpart = w;
   A.spart = (double *)(w + align256(nb * ((size_t)1 << N) * sizeof(vec2<T>)));
-  double *scale = A.spart + align256(nb * 2 * sizeof(double)) / sizeof(double);
   const int NL = N - 1;
   constexpr int RBmax = sizeof(T) == 4 ? 4 : 3;  // R = 16 (FP32) or 8 (FP64) values per thread: no spills
 #define HM_G(nl, rb) \
@@ -401,10 +396,9 @@ static int grad_t(int N, const void *const *psis, int states, double q, double *
       return fail(E_SIZE, "gradient: n = %d above the workgroup-resident limit %d", N, grad_max_n(sizeof(T) == 8));
   }
 #undef HM_G
-  hipLaunchKernelGGL(k_grad_totals, dim3(states), dim3(TOT_T), 0, st, A.spart, nblk, N, q, out, scale);
   const int64_t n = (int64_t)1 << N;
   hipLaunchKernelGGL(k_grad_reduce<T>, dim3((unsigned)((n + RED_Y - 1) / RED_Y), states), dim3(RED_Y * RED_G), 0, st,
-                     (const vec2<T> *)A.gpart, nblk, n, (const double *)scale, G);
+                     (const vec2<T> *)A.gpart, (const double *)A.spart, nblk, n, N, q, out, G);
   return hipPeekAtLastError() == hipSuccess ? OK : fail(E_HIP, "gradient launch: %s", hipGetErrorString(hipGetLastError()));
 }
 

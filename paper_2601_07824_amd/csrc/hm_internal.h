@@ -179,6 +179,12 @@ int sre_sampled_stats(const double *row_sums, const uint64_t *rows, int64_t n_ro
                       int N, double *out, hipStream_t stream);
 int sre_finalize_launch(int N, const QArgs &qa, const double *sums, double *out, hipStream_t stream);
 
+// Whole evaluations of up to seven (FP32) or six (FP64) qubits run as one launch of one workgroup
+// (hm_sre_small.hip, which states both sides of the line).
+inline bool sre_small_ok(const SrePlan &p) { return p.path == 1 && p.N <= (p.dbl ? 6 : 7); }
+int sre_small_run(const SrePlan &p, const void *psi, const QArgs &qa, double *shift_sums, double *sums, double *out,
+                  hipStream_t st);
+
 // Per-dtype drivers of the SRE kernels (one translation unit each).
 int sre_shift_sums_f32(const SrePlan &p, const void *psi, const QArgs &qa, uint64_t a0, const uint64_t *rows,
                        int64_t n_slots, double *shift_sums, char *w, hipStream_t st);

@@ -19,6 +19,7 @@
 
 #include "hm_internal.h"
 #include "hm_tile.h"
+#include "hm_totals.h"
 
 namespace hm {
 
@@ -154,17 +155,16 @@ __device__ __forceinline__ void relayout3_any(T (&re)[pow3c(RT)], T (&im)[pow3c(
   else relayout3<T, RT, SA, SB, ROWLEN>(re, im, lds, g, tp, act);
 }
 
-// Block-wide FP64 sum of three per-thread values into acc[blockIdx] (added to what is there).
-template <int NT>
+// Block-wide FP64 sum of three per-thread values into acc[blockIdx] (ADD: added to what is there).
+template <int NT, bool ADD>
 __device__ __forceinline__ void block_acc3(double v0, double v1, double v2, double *red, double *acc, uint32_t tau) {
   double v[3] = {v0, v1, v2};
 #pragma unroll
   for (int k = 0; k < 3; ++k) v[k] = seg_sum<NT, NT>(v[k], red + k * (NT / 64 + 1), tau);
   if (tau == 0) {
     double *a = acc + (size_t)blockIdx.x * 3;
-    a[0] += v[0];
-    a[1] += v[1];
-    a[2] += v[2];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) a[k] = ADD ? a[k] + v[k] : v[k];
   }
 }
 
@@ -271,7 +271,7 @@ __global__ __launch_bounds__(NT) void k_mana_rowpass(ManaRowArgs A) {
     s_acc += (double)s;
     q_acc += (double)q;
   }
-  block_acc3<NT>(m_acc, s_acc, q_acc, red, A.acc, tau);
+  block_acc3<NT, false>(m_acc, s_acc, q_acc, red, A.acc, tau);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -782,7 +782,7 @@ __global__ __launch_bounds__(NT, ManaWaves<T>::col) void k_mana_colpass(ManaColA
       q_acc += (double)q;
     }
   }
-  block_acc3<NT>(m_acc, s_acc, q_acc, red, A.acc, tau);
+  block_acc3<NT, true>(m_acc, s_acc, q_acc, red, A.acc, tau);
 }
 
 __global__ void k_mana_zero(double *p, int64_t n) {
@@ -791,31 +791,24 @@ __global__ void k_mana_zero(double *p, int64_t n) {
 }
 
 // Fixed-order sum of the per-block accumulators; sums = {m, sum chi, sum chi^2}; out = finalised.
-__global__ __launch_bounds__(256) void k_mana_total(const double *acc, int64_t nblk, int N, double *sums, double *out) {
-  __shared__ double red[256];
+static constexpr int MANA_TOT_NT = 1024;
+__global__ __launch_bounds__(MANA_TOT_NT) void k_mana_total(const double *acc, int64_t nblk, int N, double *sums,
+                                                           double *out) {
+  __shared__ double red[3 * MANA_TOT_NT / 64];
   __shared__ double tot[3];
+  double s[3] = {0.0, 0.0, 0.0};
+  for (int64_t i = threadIdx.x; i < nblk; i += MANA_TOT_NT)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) s[k] += acc[i * 3 + k];
+  block_sums<MANA_TOT_NT, 3>(s, 3, red, tot);
   const uint32_t t = threadIdx.x;
-  for (int k = 0; k < 3; ++k) {
-    double s = 0.0;
-    for (int64_t i = t; i < nblk; i += 256) s += acc[i * 3 + k];
-    red[t] = s;
-    __syncthreads();
-    for (uint32_t w = 128; w > 0; w >>= 1) {
-      if (t < w) red[t] += red[t + w];
-      __syncthreads();
-    }
-    if (t == 0) tot[k] = red[0];
-    __syncthreads();
-  }
-  if (t == 0) {
-    if (sums)
-      for (int k = 0; k < 3; ++k) sums[k] = tot[k];
+  if (t < 3) {
+    if (sums) sums[t] = tot[t];
     if (out) {
       double D = 1.0;
       for (int i = 0; i < N; ++i) D *= 3.0;
-      out[0] = log2(tot[0] / D);  // Eq. mana2: log2(sum_u |<psi|A_u|psi>| / 3^N)
-      out[1] = tot[1] / D;        // sum_u W(u)
-      out[2] = tot[2] / D;        // 3^N sum_u W(u)^2
+      // Eq. mana2: log2(sum_u |<psi|A_u|psi>| / 3^N); sum_u W(u); 3^N sum_u W(u)^2
+      out[t] = t == 0 ? log2(tot[0] / D) : tot[t] / D;
     }
   }
 }
@@ -897,16 +890,20 @@ int mana_workspace(int N, int dbl, int64_t batch, int streams, size_t *bytes) {
   return OK;
 }
 
+// Workgroups of the resident kernel: one per tile up to the fixed grid (and one where there is no tile, which
+// writes zeros).  Each writes its own sums, so nothing is cleared before.
+static unsigned mana_resident_grid(int64_t tiles) { return (unsigned)(tiles < 1 ? 1 : tiles < MANA_GRID ? tiles : MANA_GRID); }
+
 template <typename T, int RT, int NL>
-static void launch_mana_resident_nl(ManaRowArgs A, hipStream_t st) {
+static void launch_mana_resident_nl(ManaRowArgs &A, hipStream_t st) {
   constexpr int G = mana_rows_per_tile(MANA_NT, pow3c(NL - RT), false);
   A.n_tiles = (A.n_pairs + G - 1) / G;
   ProfScope prof("mana_rowpass_resident", st);
-  hipLaunchKernelGGL((k_mana_rowpass<T, MANA_NT, RT, NL>), dim3(MANA_GRID), dim3(MANA_NT), 0, st, A);
+  hipLaunchKernelGGL((k_mana_rowpass<T, MANA_NT, RT, NL>), dim3(mana_resident_grid(A.n_tiles)), dim3(MANA_NT), 0, st, A);
 }
 
 template <typename T, int RT>
-static int launch_mana_resident(int NL, ManaRowArgs A, hipStream_t st) {
+static int launch_mana_resident(int NL, ManaRowArgs &A, hipStream_t st) {
 #define HM_MROW(nl)                                  \
   case nl:                                           \
     launch_mana_resident_nl<T, RT, nl>(A, st);       \
@@ -1006,10 +1003,6 @@ static int mana_t(const ManaPlan &P, const void *psi, uint64_t a0, uint64_t a1, 
   const size_t accb = mana_acc_bytes(P);
   double *acc_row = (double *)w;
   double *acc_col = (double *)(w + accb);  // lane l: acc_col + l * MANA_GRID * 3 (contiguous)
-  {
-    const int64_t nz = (int64_t)(accb * (1 + P.lanes) / sizeof(double));
-    hipLaunchKernelGGL(k_mana_zero, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, acc_row, nz);
-  }
   int e = OK;
   if (P.path == 1) {
     const int64_t n_pairs = (int64_t)((a1 - a0 + 1) / 2);
@@ -1031,8 +1024,13 @@ static int mana_t(const ManaPlan &P, const void *psi, uint64_t a0, uint64_t a1, 
       else e = launch_mana_resident<T, 1>(P.nl, A, st);
     }
     if (e) return e;
-    hipLaunchKernelGGL(k_mana_total, dim3(1), dim3(256), 0, st, acc_row, (int64_t)MANA_GRID, P.N, sums, out);
+    hipLaunchKernelGGL(k_mana_total, dim3(1), dim3(MANA_TOT_NT), 0, st, acc_row, (int64_t)mana_resident_grid(A.n_tiles), P.N,
+                       sums, out);
     return hipPeekAtLastError() == hipSuccess ? OK : fail(E_HIP, "mana launch: %s", hipGetErrorString(hipGetLastError()));
+  }
+  {
+    const int64_t nz = (int64_t)(accb * P.lanes / sizeof(double));
+    hipLaunchKernelGGL(k_mana_zero, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, acc_col, nz);
   }
   // Two-pass: batch k runs on lane k mod lanes (lane 0 = the caller's stream, lane 1 = the internal
   // side stream, forked after the zeroing and joined before the totals), with that lane's exchange
@@ -1104,7 +1102,7 @@ static int mana_t(const ManaPlan &P, const void *psi, uint64_t a0, uint64_t a1, 
   }
   if (e) return e;
   // fixed-order sum over the lanes' per-block accumulators (contiguous)
-  hipLaunchKernelGGL(k_mana_total, dim3(1), dim3(256), 0, st, acc_col, (int64_t)MANA_GRID * P.lanes, P.N, sums, out);
+  hipLaunchKernelGGL(k_mana_total, dim3(1), dim3(MANA_TOT_NT), 0, st, acc_col, (int64_t)MANA_GRID * P.lanes, P.N, sums, out);
   return hipPeekAtLastError() == hipSuccess ? OK : fail(E_HIP, "mana launch: %s", hipGetErrorString(hipGetLastError()));
 }
 

@@ -25,6 +25,7 @@
 #include <stdint.h>
 
 #include "hm_tile.h"
+#include "hm_totals.h"
 
 namespace hm {
 
@@ -39,39 +40,19 @@ int sre_states_f32(const SrePlan &p, const void *const *psis, int n_states, cons
 int sre_states_f64(const SrePlan &p, const void *const *psis, int n_states, const QArgs &qa, double *shift_sums,
                    hipStream_t st);
 
-__device__ __forceinline__ void sre_finalize_into(const double *tot, int N, const QArgs &qa, double *out) {
-  const double D = ldexp(1.0, N);
-  for (int i = 0; i < qa.nq; ++i) {
-    const double q = qa.q[i];
-    out[i] = (q == 1.0) ? -tot[1 + i] / D : log2(tot[1 + i] / D) / (1.0 - q);
-  }
-  out[qa.nq] = 1.0 - tot[0] / D;
-}
+static constexpr int TOT_NT = 1024;
 
 // One block per state: fixed-order sum of the state's 2^N per-shift sums, finalised (Eq. sre).
 struct StateOuts {
   double *out[HM_BATCH_PTRS];
 };
-__global__ __launch_bounds__(256) void k_sre_state_totals(const double *shift_sums, int N, int nacc, QArgs qa,
-                                                          StateOuts outs) {
-  __shared__ double red[256];
+__global__ __launch_bounds__(TOT_NT) void k_sre_state_totals(const double *shift_sums, int N, int nacc, QArgs qa,
+                                                             StateOuts outs) {
+  __shared__ double red[(HM_MAX_Q + 1) * TOT_NT / 64];
   __shared__ double tot[HM_MAX_Q + 1];
-  const uint32_t t = threadIdx.x;
   const int64_t ns = (int64_t)1 << N;
-  const double *base = shift_sums + (int64_t)blockIdx.x * ns * nacc;
-  for (int k = 0; k < nacc; ++k) {
-    double s = 0.0;
-    for (int64_t i = t; i < ns; i += 256) s += base[i * nacc + k];
-    red[t] = s;
-    __syncthreads();
-    for (uint32_t w = 128; w > 0; w >>= 1) {
-      if (t < w) red[t] += red[t + w];
-      __syncthreads();
-    }
-    if (t == 0) tot[k] = red[0];
-    __syncthreads();
-  }
-  if (t == 0) sre_finalize_into(tot, N, qa, outs.out[blockIdx.x]);
+  block_rows_sum<TOT_NT>(shift_sums + (int64_t)blockIdx.x * ns * nacc, ns, nacc, red, tot);
+  sre_finalize_into(tot, N, qa, outs.out[blockIdx.x]);
 }
 
 // Monte Carlo M_2 from sampled X-rows, with the a = 0 row (which holds the identity, <I>^4 = 1, a
@@ -125,67 +106,26 @@ __global__ __launch_bounds__(256) void k_sre_sampled_stats(const double *row_sum
   }
 }
 
-// Fixed-order sum of rows [0, n) of nacc doubles by one workgroup: thread t adds the rows
-// t, t + TOT_NT, ... (all nacc slots of a row at once), then a tree over the threads per slot.
-// tot[k] (shared) receives the sums.
-static constexpr int TOT_NT = 1024;
-__device__ __forceinline__ void block_rows_sum(const double *rows_, int64_t n, int nacc, double *red, double *tot) {
-  const uint32_t t = threadIdx.x;
-  double s[HM_MAX_Q + 1];
-#pragma unroll
-  for (int k = 0; k <= HM_MAX_Q; ++k) s[k] = 0.0;
-  for (int64_t i = t; i < n; i += TOT_NT) {
-    const double *row = rows_ + i * nacc;
-#pragma unroll
-    for (int k = 0; k <= HM_MAX_Q; ++k)
-      if (k < nacc) s[k] += row[k];
-  }
-#pragma unroll
-  for (int k = 0; k <= HM_MAX_Q; ++k) {
-    if (k < nacc) {  // uniform across the workgroup
-      red[t] = s[k];
-      __syncthreads();
-      for (uint32_t w = TOT_NT / 2; w > 0; w >>= 1) {
-        if (t < w) red[t] += red[t + w];
-        __syncthreads();
-      }
-      if (t == 0) tot[k] = red[0];
-      __syncthreads();
-    }
-  }
-}
-
 // First level for long shift lists: workgroup g sums the contiguous chunk of rows
 // [g chunk, (g + 1) chunk) into part[g] (fixed order within and across workgroups).
 __global__ __launch_bounds__(TOT_NT) void k_sre_total_part(const double *shift_sums, int64_t n_slots, int nacc,
                                                            int64_t chunk, double *part) {
-  __shared__ double red[TOT_NT];
+  __shared__ double red[(HM_MAX_Q + 1) * TOT_NT / 64];
   __shared__ double tot[HM_MAX_Q + 1];
   const int64_t r0 = (int64_t)blockIdx.x * chunk;
   const int64_t n = r0 >= n_slots ? 0 : (n_slots - r0 < chunk ? n_slots - r0 : chunk);
-  block_rows_sum(shift_sums + r0 * nacc, n, nacc, red, tot);
-  if (threadIdx.x == 0)
-    for (int k = 0; k < nacc; ++k) part[blockIdx.x * nacc + k] = tot[k];
+  block_rows_sum<TOT_NT>(shift_sums + r0 * nacc, n, nacc, red, tot);
+  if (threadIdx.x < (uint32_t)nacc) part[blockIdx.x * nacc + threadIdx.x] = tot[threadIdx.x];
 }
 
 // Fixed-order sum over all per-shift sums (or first-level partials); optionally finalise (Eq. sre).
 __global__ __launch_bounds__(TOT_NT) void k_sre_total(const double *shift_sums, int64_t n_slots, int nacc, QArgs qa,
                                                       int N, double *sums, double *out) {
-  __shared__ double red[TOT_NT];
+  __shared__ double red[(HM_MAX_Q + 1) * TOT_NT / 64];
   __shared__ double tot[HM_MAX_Q + 1];
-  block_rows_sum(shift_sums, n_slots, nacc, red, tot);
-  if (threadIdx.x == 0) {
-    if (sums)
-      for (int k = 0; k < nacc; ++k) sums[k] = tot[k];
-    if (out) {
-      const double D = ldexp(1.0, N);
-      for (int i = 0; i < qa.nq; ++i) {
-        const double q = qa.q[i];
-        out[i] = (q == 1.0) ? -tot[1 + i] / D : log2(tot[1 + i] / D) / (1.0 - q);
-      }
-      out[qa.nq] = 1.0 - tot[0] / D;
-    }
-  }
+  block_rows_sum<TOT_NT>(shift_sums, n_slots, nacc, red, tot);
+  if (sums && threadIdx.x < (uint32_t)nacc) sums[threadIdx.x] = tot[threadIdx.x];
+  if (out) sre_finalize_into(tot, N, qa, out);
 }
 
 // ---- internal streams -----------------------------------------------------------------------------
@@ -310,6 +250,9 @@ int sre_run(const SrePlan &p, const void *psi, const QArgs &qa, uint64_t a0, con
     ss = (double *)w;
     w += align256((size_t)n_slots * (size_t)nacc_of(qa) * sizeof(double));
   }
+  // a whole evaluation that fits one workgroup is one launch
+  if (p.path == 1 && !rows && a0 == 0 && n_slots == (int64_t)1 << p.N && (sums || out) && sre_small_ok(p))
+    return sre_small_run(p, psi, qa, ss, sums, out, st);
   int e = p.dbl ? sre_shift_sums_f64(p, psi, qa, a0, rows, n_slots, ss, w, st)
                 : sre_shift_sums_f32(p, psi, qa, a0, rows, n_slots, ss, w, st);
   if (e) return e;
@@ -356,7 +299,7 @@ int sre_run_states(const SrePlan &p, const void *const *psis, int n_states, cons
   StateOuts o{};
   for (int i = 0; i < n_states; ++i) o.out[i] = outs[i];
   ProfScope prof("sre_state_totals", st);
-  hipLaunchKernelGGL(k_sre_state_totals, dim3(n_states), dim3(256), 0, st, ss, p.N, nacc_of(qa), qa, o);
+  hipLaunchKernelGGL(k_sre_state_totals, dim3(n_states), dim3(TOT_NT), 0, st, ss, p.N, nacc_of(qa), qa, o);
   return hipPeekAtLastError() == hipSuccess ? OK : fail(E_HIP, "SRE batched totals: %s", hipGetErrorString(hipGetLastError()));
 }
 
@@ -366,15 +309,7 @@ int sre_sampled_stats(const double *row_sums, const uint64_t *rows, int64_t n_ro
   return hipPeekAtLastError() == hipSuccess ? OK : fail(E_HIP, "SRE sampled stats: %s", hipGetErrorString(hipGetLastError()));
 }
 
-__global__ void k_sre_finalize(int N, QArgs qa, const double *sums, double *out) {
-  if (threadIdx.x != 0) return;
-  const double D = ldexp(1.0, N);
-  for (int i = 0; i < qa.nq; ++i) {
-    const double q = qa.q[i];
-    out[i] = (q == 1.0) ? -sums[1 + i] / D : log2(sums[1 + i] / D) / (1.0 - q);
-  }
-  out[qa.nq] = 1.0 - sums[0] / D;
-}
+__global__ void k_sre_finalize(int N, QArgs qa, const double *sums, double *out) { sre_finalize_into(sums, N, qa, out); }
 
 int sre_finalize_launch(int N, const QArgs &qa, const double *sums, double *out, hipStream_t st) {
   hipLaunchKernelGGL(k_sre_finalize, dim3(1), dim3(64), 0, st, N, qa, sums, out);
