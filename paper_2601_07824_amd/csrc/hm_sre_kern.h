@@ -582,13 +582,15 @@ static void launch_row_occ(RowPassArgs A, int qm, hipStream_t st) {
     const dim3 grid((unsigned)grid_for(A.n_tiles - A.tile0)), block(NT);
     if (qm == 2) hipLaunchKernelGGL((k_sre_rowpass_occ<T, NT, RB, NL, 2, MINW>), grid, block, 0, st, A);
     else if (qm == 1) hipLaunchKernelGGL((k_sre_rowpass_occ<T, NT, RB, NL, 1, MINW>), grid, block, 0, st, A);
-    else hipLaunchKernelGGL((k_sre_rowpass_occ<T, NT, RB, NL, 0, (MINW > 3 ? 3 : MINW)>), grid, block, 0, st, A);
+    else hipLaunchKernelGGL((k_sre_rowpass_occ<T, NT, RB, NL, 0, MINW>), grid, block, 0, st, A);
   }
 }
 
 // split: tiles of 2^10..2^14 (FP32) / 2^10..2^13 (FP64) values use split LDS staging and a register
 // budget of at least 3 waves per SIMD (4 for 2^14 FP32 values: 512 threads x 32 values in 128
-// registers); one tile per workgroup, the tiles use about 100 registers.
+// registers, also for any indices, where the power function spills 61 of them: two
+// workgroups per CU, 8 indices at N = 15 24.9 ms against 33.0 ms with one); one tile per workgroup, the
+// tiles use about 100 registers.
 template <typename T>
 static int launch_resident(int NL, RowPassArgs A, int qm, hipStream_t st, bool split = false) {
   constexpr int RB = ResidentRB<T>::value;

@@ -355,8 +355,7 @@ __device__ __forceinline__ T sum_kind(T (&re)[R], T (&im)[R], QKind kind, double
 // QM == 0: any q.  Measured for q = (1, 2, 3) on MI355X against all kinds unrolled with one accumulator
 // per q: complex64 N = 13 142 -> 78 us, N = 16 11.3 -> 6.3 ms; complex128 N = 15 15.6 -> 10.5 ms.
 // Eight other indices: complex128 N = 8 163 -> 122 us, N = 14 22.5 -> 13.1 ms; complex64 N = 8 204 -> 189 us,
-// N = 13 and 14 as before, N = 15 25.8 -> 33.0 ms (its registers leave room for one workgroup per CU, not two;
-// held to the budget of two they spill and it takes the same 33 ms).
+// N = 13 1725 -> 1713 us, N = 15 25.8 -> 24.9 ms.
 template <typename T, int R, int NT, int SEG, int QM, typename F>
 __device__ __forceinline__ void tile_sums(T (&re)[R], T (&im)[R], const QArgs &qa, double *red, uint32_t tau, F out) {
   if constexpr (QM == 2) {
