@@ -3,10 +3,10 @@
 //
 // All 2^N shift vectors of 2^(N-1) folded values are at most 2^13 values, one workgroup tile.  What such a call
 // costs is its launches: the tile pass over several workgroups and the sum over the shifts are 6.3 + 3.1 us of
-// kernels and a gap, one workgroup doing both takes 8.9 us at N = 7 (a whole call: 9.1 us at N = 7, 8.0 to
-// 8.5 us at N <= 6, against 10.7 us in two launches at N = 8).  Above the line the one workgroup's own work is the longer: complex64 N = 8 14.9 against 10.7 us,
-// complex128 N = 7 with q = (1, 2, 3) 20.6 against 16.3 us.  The tile is the resident row pass's (same rounds, same
-// sums per shift).
+// kernels and a gap, one workgroup doing both takes 8.9 us at N = 7 (a whole call: 9.1 us at N = 7, 8.0 to 8.5 us
+// at N <= 6, against 10.7 us in two launches at N = 8).  Above the line the one workgroup's own work is the
+// longer: complex64 N = 8 14.9 against 10.7 us, complex128 N = 7 with q = (1, 2, 3) 20.6 against 16.3 us.  The
+// tile is the resident row pass's (same rounds, same sums per shift).
 #include "hm_sre_kern.h"
 #include "hm_totals.h"
 
