@@ -148,6 +148,9 @@ __global__ __launch_bounds__(NT, fused_waves(RB, sizeof(T))) void k_grad_rowback
   const T q4 = (T)(4.0 * F.q);
 
   for (uint32_t i = tau; i < (uint32_t)(G * ROW); i += NT) slice[i] = vec2<T>{T(0), T(0)};
+  // A wave adds into its own row tasks' slices, which other waves zeroed, and the re-layouts of the shift loop
+  // (all inside a wave) do not order the waves.
+  __syncthreads();
   T axr[R], axi[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) axr[r] = axi[r] = T(0);
