@@ -41,6 +41,9 @@ __global__ __launch_bounds__(NT) void k_sre_rowback(RowPassArgs A) {
   constexpr int S0 = NL - RB;
   constexpr int K = (NL + RB - 1) / RB;
   static_assert(K >= 2 && K <= 4, "two to four rounds");
+  // a tile's moves end reading layout S0 and the next tile's begin writing the first layout, with no barrier
+  // between: every wave has to stay in its own stretch of lds
+  static_assert(S0 <= 6, "re-layouts stay inside a wave");
   constexpr int SEG = 1 << S0;
   constexpr int G = 1 << (TB - NL);
   vec2<T> *__restrict__ ex = (vec2<T> *)A.exch;
@@ -124,6 +127,9 @@ __global__ __launch_bounds__(NT, fused_waves(RB, sizeof(T))) void k_grad_rowback
   constexpr int S0 = NL - RB;
   constexpr int K = (NL + RB - 1) / RB;
   static_assert(K >= 2 && K <= 4, "two to four rounds");
+  // a row task is one wave's: its slice is read and written across lanes, and the shift loop's moves go from
+  // layout S0 back to the first layout, both without a barrier
+  static_assert(S0 <= 6, "re-layouts and slices stay inside a wave");
   constexpr int SEG = 1 << S0;       // threads per row task
   constexpr int G = 1 << (TB - NL);  // row tasks (shifts in flight) per workgroup
   constexpr int ROW = 1 << NL;

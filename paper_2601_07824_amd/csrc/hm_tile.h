@@ -155,6 +155,9 @@ __device__ __forceinline__ void wht_lanes(T (&re)[R], T (&im)[R], uint32_t tau) 
 //   * otherwise a barrier separates the writes from the reads.  One before the writes is needed only
 //     when they go to other waves' stretches (SA > 6): consecutive moves chain (the layout read last is
 //     the layout written next), so for SA <= 6 every wave last read its own stretch.
+// So a move orders the traffic of its own buffer only, and only along a chain of moves.  A caller may not use it as
+// a barrier for other LDS arrays, and a loop whose moves end in a layout other than the one written first puts a
+// barrier between its iterations or asserts that both have S <= 6.
 // Without the barriers the waves of a workgroup drift apart and one wave's LDS traffic overlaps
 // another's butterflies (barriers per FP32 row tile of 2^15 values: 8 -> 4, of 2^11 values: 8 -> 0).
 __device__ __forceinline__ void wave_order() {
