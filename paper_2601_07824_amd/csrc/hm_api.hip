@@ -493,17 +493,14 @@ static int batched_ws(hm_handle h, const int *ns, int batch, int dbl, int n_q, s
   std::vector<int> pers, rest;
   batched_split(h, ns, batch, dbl, &pers, &rest);
   if (!pers.empty()) need = batch_persistent_workspace(ns, pers.data(), (int)pers.size(), n_q, dbl);
-  for (int i : rest) {
+  int count[32] = {};  // by size: a pass over all pairs of states costs more than the kernels of 4096 states of n = 10
+  for (int i : rest) ++count[ns[i]];
+  for (int n = 0; n < 32; ++n) {
+    if (!count[n]) continue;
     SrePlan p;
-    sre_plan(ns[i], dbl, plan_opts(h, ns[i], dbl), &p);
-    size_t b;
-    if (p.path == 1) {
-      int cnt = 0;
-      for (int j : rest) cnt += ns[j] == ns[i];
-      b = sre_states_workspace(p, n_q, cnt < HM_BATCH_PTRS ? cnt : HM_BATCH_PTRS);
-    } else {
-      b = sre_workspace(p, n_q, (int64_t)1 << ns[i]);
-    }
+    sre_plan(n, dbl, plan_opts(h, n, dbl), &p);
+    const size_t b = p.path == 1 ? sre_states_workspace(p, n_q, count[n] < HM_BATCH_PTRS ? count[n] : HM_BATCH_PTRS)
+                                 : sre_workspace(p, n_q, (int64_t)1 << n);
     if (b > need) need = b;
   }
   *bytes = need;
