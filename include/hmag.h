@@ -272,8 +272,8 @@ hm_status hm_sre_batched_grad(hm_handle h, const void *const *psis, const int *n
  * (no host-to-device copy).  One workgroup per state then sums its per-shift sums in a fixed order,
  * so results are deterministic and equal hm_sre's up to the order of the FP64 sums and the FP32
  * tile shape.  Smaller states run by size class (up to 64 per launch) and two-pass sizes one after
- * another, after the persistent launch, on the same workspace.  Workspace:
- * hm_sre_batched_workspace. */
+ * another, after the persistent launch, on the same workspace.  Workspace: hm_sre_batched_workspace
+ * (with the launch form left automatic, the larger of the two forms'). */
 hm_status hm_sre_batched_workspace(hm_handle h, const int *ns, int batch, hm_dtype dtype, int n_q,
                                    size_t *bytes);
 hm_status hm_sre_batched(hm_handle h, const void *const *psis, const int *ns, int batch, hm_dtype dtype,

@@ -467,10 +467,8 @@ static int batched_auto_mode(hm_handle h, const int *ns, int batch, int dbl) {
 // options, at least 2^RB folded values) go to one persistent launch; the rest (tiny states, two-pass
 // sizes; all states in the per-class form) run by size class / one after another on the same workspace
 // after it.
-static void batched_split(hm_handle h, const int *ns, int batch, int dbl, std::vector<int> *pers,
+static void batched_split(hm_handle h, const int *ns, int batch, int dbl, int mode, std::vector<int> *pers,
                           std::vector<int> *rest) {
-  const int mode = h->opts.batch_launch ? h->opts.batch_launch
-                   : h->tuned_batch_launch ? h->tuned_batch_launch : batched_auto_mode(h, ns, batch, dbl);
   for (int i = 0; i < batch; ++i) {
     if (mode == 2) {
       rest->push_back(i);
@@ -482,16 +480,14 @@ static void batched_split(hm_handle h, const int *ns, int batch, int dbl, std::v
   }
 }
 
-static int batched_ws(hm_handle h, const int *ns, int batch, int dbl, int n_q, size_t *bytes) {
-  if (!ns || batch < 1) return fail(E_ARG, "batched: ns is NULL or batch = %d < 1", batch);
+// The launch form set or tuned on the handle, 0 if neither.
+static int batched_set_mode(hm_handle h) { return h->opts.batch_launch ? h->opts.batch_launch : h->tuned_batch_launch; }
+
+// Workspace of one launch form.
+static size_t batched_form_ws(hm_handle h, const int *ns, int batch, int dbl, int n_q, int mode) {
   size_t need = 256;
-  for (int i = 0; i < batch; ++i) {
-    SrePlan p;
-    int st = sre_plan(ns[i], dbl, plan_opts(h, ns[i], dbl), &p);
-    if (st) return st;
-  }
   std::vector<int> pers, rest;
-  batched_split(h, ns, batch, dbl, &pers, &rest);
+  batched_split(h, ns, batch, dbl, mode, &pers, &rest);
   if (!pers.empty()) need = batch_persistent_workspace(ns, pers.data(), (int)pers.size(), n_q, dbl);
   int count[32] = {};  // by size: a pass over all pairs of states costs more than the kernels of 4096 states of n = 10
   for (int i : rest) ++count[ns[i]];
@@ -503,7 +499,16 @@ static int batched_ws(hm_handle h, const int *ns, int batch, int dbl, int n_q, s
                                  : sre_workspace(p, n_q, (int64_t)1 << n);
     if (b > need) need = b;
   }
-  *bytes = need;
+  return need;
+}
+
+static int batched_check(hm_handle h, const int *ns, int batch, int dbl) {
+  if (!ns || batch < 1) return fail(E_ARG, "batched: ns is NULL or batch = %d < 1", batch);
+  for (int i = 0; i < batch; ++i) {
+    SrePlan p;
+    int st = sre_plan(ns[i], dbl, plan_opts(h, ns[i], dbl), &p);
+    if (st) return st;
+  }
   return OK;
 }
 
@@ -512,7 +517,13 @@ hm_status hm_sre_batched_workspace(hm_handle h, const int *ns, int batch, hm_dty
   if (!h || !bytes) return (hm_status)fail(E_ARG, "h or bytes is NULL");
   HM_TRY(check_dtype(dtype));
   if (n_q < 1 || n_q > HM_MAX_Q) return (hm_status)fail(E_ARG, "n_q = %d outside [1, %d]", n_q, HM_MAX_Q);
-  return (hm_status)batched_ws(h, ns, batch, dtype == HM_C128, n_q, bytes);
+  const int dbl = dtype == HM_C128, mode = batched_set_mode(h);
+  HM_TRY(batched_check(h, ns, batch, dbl));
+  // left automatic: either form, so that it also holds for the autotuner and once that has chosen
+  const size_t pers = mode == 2 ? 0 : batched_form_ws(h, ns, batch, dbl, n_q, 1);
+  const size_t classes = mode == 1 ? 0 : batched_form_ws(h, ns, batch, dbl, n_q, 2);
+  *bytes = pers > classes ? pers : classes;
+  return HM_OK;
 }
 
 hm_status hm_sre_batched(hm_handle h, const void *const *psis, const int *ns, int batch, hm_dtype dtype,
@@ -525,13 +536,13 @@ hm_status hm_sre_batched(hm_handle h, const void *const *psis, const int *ns, in
   QArgs qa;
   HM_TRY(check_q(q, n_q, &qa));
   const int dbl = dtype == HM_C128;
-  size_t need;
-  HM_TRY(batched_ws(h, ns, batch, dbl, n_q, &need));
+  HM_TRY(batched_check(h, ns, batch, dbl));
+  const int mode = batched_set_mode(h) ? batched_set_mode(h) : batched_auto_mode(h, ns, batch, dbl);
   for (int i = 0; i < batch; ++i) HM_TRY(check_ptr(psis[i], psi_align(dtype), "psis[i]"));
-  HM_TRY(check_ws(ws, ws_bytes, need));
+  HM_TRY(check_ws(ws, ws_bytes, batched_form_ws(h, ns, batch, dbl, n_q, mode)));
   for (int i = 0; i < batch; ++i) HM_TRY(norm_ok(h, psis[i], 2, ns[i], dtype, stream));
   std::vector<int> pers, rest;
-  batched_split(h, ns, batch, dbl, &pers, &rest);
+  batched_split(h, ns, batch, dbl, mode, &pers, &rest);
   HM_TRY(batch_persistent_run(dbl, psis, ns, pers.data(), (int)pers.size(), qa, out, ws, stream));
   // the rest: resident size classes up to HM_BATCH_PTRS states per launch, two-pass states one by one
   std::vector<char> done(batch, 0);

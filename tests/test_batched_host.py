@@ -31,3 +31,15 @@ def test_planning_grows_with_the_batch(mode):
             out.append(time.perf_counter() - t)
         return min(out)
     assert best(32768) < 24 * best(4096)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("ns", [[11] * 64, [9, 10, 11, 12, 13, 14] * 200, [5, 6, 7], [17, 12, 3]])
+def test_automatic_workspace_covers_both_forms(ns, dtype):
+    """hm_autotune_batched may choose either form, for itself and for later calls on the workspace at hand."""
+    forms = []
+    for mode in (0, 1, 2):
+        ctx = hm.Context()
+        ctx.set_option(hm.OPT_BATCH_LAUNCH, mode)
+        forms.append([workspace(ctx, ns, dtype, n_q) for n_q in (1, 3)])
+    assert forms[0] == [max(a, b) for a, b in zip(forms[1], forms[2])], forms
