@@ -448,8 +448,15 @@ hm_status hm_sre_batched_grad(hm_handle h, const void *const *psis, const int *n
 // 0.6e12/s, but is one launch, where the classes cost two launches (about 10 us) per 64 states of a class.
 // So the classes win once their strings outweigh their launches.  Measured on MI355X (complex64, persistent
 // against classes): 48 states n = 9..14 2663 / 1514 us, 16 states n = 12..13 634 / 349, 64 states n = 11 288 /
-// 134, 60 states n = 7..11 97 / 93; 8 states n = 7..11 34 / 58, 1000 states n = 5..9 1006 / 1607.
-static int batched_auto_mode(hm_handle h, const int *ns, int batch, int dbl) {
+// 134, 60 states n = 7..11 97 / 93; 8 states n = 7..11 34 / 58, 1000 states n = 5..9 1006 / 1607.  complex128 48
+// states 5095 / 2872, 60 states 127 / 92, 8 states 34 / 46; q = (1, 2, 3) 60 states 138 / 129, complex128 317 / 311.
+// With other indices pow takes most of the time in either form, and small classes fill the chip worse than one
+// launch, so a launch has to bring 4e7 strings: q = 0.5 60 states n = 7..11 319 / 364 (complex128 461 / 490), 24
+// states n = 9..10 100 / 123 (135 / 131), 20 states n = 8..12 406 / 408 (614 / 625); 2 states n = 12, 13 377 / 312
+// (576 / 557), 64 states n = 11 1157 / 856 (1748 / 1702).
+static int batched_auto_mode(hm_handle h, const int *ns, int batch, int dbl, const QArgs &qa) {
+  bool power = false;
+  for (int i = 0; i < qa.nq; ++i) power |= qa.q[i] != 1.0 && qa.q[i] != 2.0 && qa.q[i] != 3.0 && qa.q[i] != 4.0;
   double strings = 0.0;  // of the states the persistent launch could take
   int count[32] = {};
   for (int i = 0; i < batch; ++i) {
@@ -460,7 +467,7 @@ static int batched_auto_mode(hm_handle h, const int *ns, int batch, int dbl) {
   }
   int launches = 0;
   for (int n = 0; n < 32; ++n) launches += (count[n] + HM_BATCH_PTRS - 1) / HM_BATCH_PTRS;
-  return strings > 1.2e7 * (launches - 1) ? 2 : 1;
+  return strings > (power ? 4e7 : 1.2e7) * (launches - 1) ? 2 : 1;
 }
 
 // Batched calls in the persistent form: states of workgroup-resident size (path 1 under the handle's
@@ -537,7 +544,7 @@ hm_status hm_sre_batched(hm_handle h, const void *const *psis, const int *ns, in
   HM_TRY(check_q(q, n_q, &qa));
   const int dbl = dtype == HM_C128;
   HM_TRY(batched_check(h, ns, batch, dbl));
-  const int mode = batched_set_mode(h) ? batched_set_mode(h) : batched_auto_mode(h, ns, batch, dbl);
+  const int mode = batched_set_mode(h) ? batched_set_mode(h) : batched_auto_mode(h, ns, batch, dbl, qa);
   for (int i = 0; i < batch; ++i) HM_TRY(check_ptr(psis[i], psi_align(dtype), "psis[i]"));
   HM_TRY(check_ws(ws, ws_bytes, batched_form_ws(h, ns, batch, dbl, n_q, mode)));
   for (int i = 0; i < batch; ++i) HM_TRY(norm_ok(h, psis[i], 2, ns[i], dtype, stream));
