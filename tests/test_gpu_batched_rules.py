@@ -23,7 +23,7 @@ def test_form_by_size_and_index_kind(ns, q, family):
     try:
         hm.sre_batched(xs, q)
         torch.cuda.synchronize()
-        ran = {k for k, v in hm.profile_read().items() if v["launches"]}
+        ran = {k for k, v in hm.profile_read().items() if v[0]}
     finally:
         hm.profile_enable(False)
     assert ran & {"sre_rowpass_resident", "sre_batch_persistent"} == {family}, ran
