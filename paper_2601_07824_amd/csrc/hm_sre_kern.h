@@ -653,11 +653,13 @@ static int launch_rowwrite_rb(int NL, RowPassArgs A, hipStream_t st) {
   // state twice through the L2s.  Row block by row block (each XCD a contiguous share, so a row block of psi_x
   // stays in its L2 for all the launch's shifts that fold on the same bit) only psi_{x^a} is streamed.  From
   // 2^18 folded values on, where the state outgrows an L2 (2048 rows, complex64 N = 22 20.5 -> 18.4 ms,
-  // complex128 N = 20 10.0 -> 8.8 ms).
+  // complex128 N = 20 10.0 -> 8.8 ms), and where a launch holds several shifts: two still gain (complex64 N = 25,
+  // 12 rows 1496 -> 1451 us), one has nothing to share and only loses its order (N = 26 3449 -> 3658 us, complex128
+  // N = 24, 32 rows 3839 -> 3959 us).
 #define HM_RW(nl, nt)                                               \
   case nl:                                                          \
     A.n_tiles = row_tiles<nt, RB, nl>(A);                           \
-    A.by_rows = A.rows && A.nf >= 18 && (nl) + A.nh >= ilog2c(nt) + RB; \
+    A.by_rows = A.rows && A.n_slots > 1 && A.nf >= 18 && (nl) + A.nh >= ilog2c(nt) + RB; \
     launch_row_q<T, nt, RB, nl, true, SPLIT>(A, false, st);         \
     return OK;
   switch (NL) {
@@ -668,7 +670,7 @@ static int launch_rowwrite_rb(int NL, RowPassArgs A, hipStream_t st) {
     case 14:
       if constexpr (sizeof(T) == 4 && NT14 <= 1024) {
         A.n_tiles = row_tiles<NT14, RB, 14>(A);
-        A.by_rows = A.rows != nullptr;
+        A.by_rows = A.rows && A.n_slots > 1;
         launch_row_q<T, NT14, RB, 14, true, SPLIT>(A, false, st);
         return OK;
       }
@@ -676,7 +678,7 @@ static int launch_rowwrite_rb(int NL, RowPassArgs A, hipStream_t st) {
     case 15:  // split staging only: whole-complex staging needs more registers than 1024 threads have
       if constexpr (sizeof(T) == 4 && NT15 <= 1024 && SPLIT) {
         A.n_tiles = row_tiles<NT15, RB, 15>(A);
-        A.by_rows = A.rows != nullptr;
+        A.by_rows = A.rows && A.n_slots > 1;
         launch_row_q<T, NT15, RB, 15, true, SPLIT>(A, false, st);
         return OK;
       }
