@@ -701,13 +701,23 @@ static int launch_rowwrite(int rb, int NL, RowPassArgs A, bool split, hipStream_
   return fail(E_UNSUPPORTED, "row pass: register tile 2^%d (split %d) not built for this dtype", rb, (int)split);
 }
 
-// Consecutive shifts: the row pass by groups of shifts (k_sre_rowgroup) for rows of 2^8..2^13 values (FP32 tiles
-// of 2^4 values per thread, the gradient's: 2^8..2^10); the shifts below one group, among them a = 0, run one
-// by one.  Returns false where it does not apply (fewer rows per shift than a tile holds).
+// Workgroups' worth of whole groups from which a range goes by groups.  A group's shifts run one after another in its
+// workgroups, so shorter ranges leave the chip idle, where shift by shift every shift has workgroups of its own.  On
+// MI355X, by groups against shift by shift: complex64 n = 17 (rows of 2^8) 64 shifts = 128 workgroups 40.2 / 39.2 us,
+// 128 shifts 41.6 / 50.1; n = 18 (2^9) 8 shifts = 32 workgroups 34.7 / 22.0, 192 40.9 / 46.3; n = 20 (2^10) 8 shifts =
+// 128 46.8 / 36.0, 384 55.6 / 51.8, 512 60.1 / 62.2; n = 22 (2^13) 128 46.6 / 45.1, 192 57.6 / 59.2; complex128
+// n = 17 128 26.8 / 23.7, 192 30.2 / 31.7, n = 20 (2^10) 256 35.8 / 32.3, 512 40.9 / 44.6.
+constexpr int64_t row_group_min(int NL) { return NL == 10 ? 512 : 192; }
+
+// Consecutive shifts: the row pass by groups of shifts (k_sre_rowgroup) for rows of 2^8..2^13 FP32 and 2^7..2^13
+// FP64 values (FP32 tiles of 2^4 values per thread, the gradient's: 2^7..2^10); the shifts below one group, among
+// them a = 0, run one by one.  Returns false where it does not apply (fewer rows per shift than a tile holds) or
+// the range is too short.
 template <typename T, int RB, int NL, int NT>
 static bool launch_rowgroup_nl(const RowPassArgs &A, int64_t skip, hipStream_t st) {
   constexpr int LG = ilog2c(NT) + RB - NL, GB = row_group_bits<T>(NL, RB);
   if (A.nh < LG) return false;
+  if (((A.n_slots - skip) << (A.nh - LG)) >> GB < row_group_min(NL)) return false;
   RowGroupArgs B{};
   B.psi = A.psi;
   B.nf = A.nf;
