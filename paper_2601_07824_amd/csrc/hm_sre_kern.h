@@ -869,12 +869,14 @@ int shift_sums_t(const SrePlan &p, const void *psi, const QArgs &qa, uint64_t a0
     if (hipEventRecord(ev_fork, st) != hipSuccess || hipStreamWaitEvent(lane[1].st, ev_fork, 0) != hipSuccess)
       return fail(E_HIP, "SRE: stream fork failed");
   }
-  int64_t bi = 0;
+  // Consecutive shifts that start inside a group of shifts (launch_rows): the first batch ends at a whole group where
+  // that takes no batch more, or one among many.
+  int64_t bi = 0, off = !rows && p.batch >= 64 && p.batch % 8 == 0 ? (int64_t)(a0 & 7u) : 0;
+  if (n_slots < 8 * (int64_t)p.batch && (n_slots + off - 1) / p.batch != (n_slots - 1) / p.batch) off = 0;
   for (int64_t s0 = 0, nb = 0; s0 < n_slots; s0 += nb, ++bi) {
     Lane &ln = lane[bi % L];
-    // a first batch that ends at a whole group of shifts (launch_rows) where consecutive shifts start inside one
-    const int64_t off = !rows && p.batch >= 64 ? (int64_t)((a0 + (uint64_t)s0) & 7u) : 0;
-    nb = (n_slots - s0) < p.batch - off ? (n_slots - s0) : p.batch - off;
+    const int64_t most = p.batch - (s0 == 0 ? off : 0);
+    nb = (n_slots - s0) < most ? (n_slots - s0) : most;
     RowPassArgs A{};
     A.psi = psi;
     A.nf = p.nf;
