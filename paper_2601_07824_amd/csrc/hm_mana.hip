@@ -508,8 +508,8 @@ __global__ __launch_bounds__(NT, ManaWaves<T>::row) void k_mana_rowfamilies(Mana
   }
 }
 
-// The same one pair (a, a + 1) at a time, every pair with its own gathers: for states so large that a launch
-// holds only a few pairs (a sextet would not fit the memory-side cache).
+// The same one pair (a, a + 1) at a time, every pair with its own gathers: for short ranges of shifts, and for states
+// so large that a launch holds only a few pairs (a sextet would not fit the memory-side cache).
 struct ManaWriteArgs {
   const void *psi;
   uint32_t psi_bytes;  // 3^N values
@@ -867,9 +867,10 @@ static int mana_plan(int N, int dbl, int64_t batch, int streams, ManaPlan *p) {
     if (b < 1) b = 1;
     // Shared gathers where the memory-side cache holds at least 12 pairs (n <= 13 complex64, 12 complex128):
     // there whole sextets fill a launch.  Larger states run pair by pair (n = 14 complex64, 500 shifts:
-    // 6.2 ms against 6.4 with one sextet per launch; n = 15, 100 shifts: 4.5 against 5.1).
-    P.families = (192ull << 20) / per_pair >= 12;
-    if (P.families) b = b < 3 ? 3 : b - b % 3;
+    // 6.2 ms against 6.4 with one sextet per launch; n = 15, 100 shifts: 4.5 against 5.1), and so do launches
+    // that the caller keeps below three pairs.
+    P.families = (192ull << 20) / per_pair >= 12 && b >= 3;
+    if (P.families) b -= b % 3;
     P.batch_pairs = (int)b;
     P.lanes = streams ? streams : MANA_STREAMS_DEFAULT;
   }
@@ -933,12 +934,14 @@ static int launch_mana_pairs_nl(ManaWriteArgs A, int nh, hipStream_t st) {
 
 template <typename T>
 static int launch_mana_pairs(int RT, int NL, int nh, ManaWriteArgs A, hipStream_t st) {
-  if (RT == 3 && NL == 8) return launch_mana_pairs_nl<T, 3, 8>(A, nh, st);
+#define HM_MPAIR(rt, nl) \
+  if (RT == rt && NL == nl) return launch_mana_pairs_nl<T, rt, nl>(A, nh, st);
   if constexpr (sizeof(T) == 4) {
-    if (RT == 3 && NL == 7) return launch_mana_pairs_nl<T, 3, 7>(A, nh, st);
+    HM_MPAIR(3, 5) HM_MPAIR(3, 6) HM_MPAIR(3, 7) HM_MPAIR(3, 8)
   } else {
-    if (RT == 2 && NL == 7) return launch_mana_pairs_nl<T, 2, 7>(A, nh, st);
+    HM_MPAIR(2, 4) HM_MPAIR(2, 5) HM_MPAIR(2, 6) HM_MPAIR(2, 7) HM_MPAIR(3, 8)
   }
+#undef HM_MPAIR
   return fail(E_UNSUPPORTED, "mana: no row-pass kernel for rows of 3^%d (RT %d)", NL, RT);
 }
 
@@ -996,6 +999,18 @@ static int launch_mana_col(int NH, int nl, ManaColArgs A, hipStream_t st) {
   return fail(E_UNSUPPORTED, "mana: no column kernel for 3^%d rows", NH);
 }
 
+// Whether the shifts [a0, a1) go by sextets: they have to fill the chip (a sextet's pairs run one after another in a
+// workgroup) and most of their own sextets (absent shifts cost like present ones).  On MI355X, by families against
+// pair by pair: complex64 n = 11 (81 workgroups a sextet) 18 aligned shifts 26.0 / 26.7 us, 24 28.8 / 32.2; n = 12 (243)
+// one shift 27.9 / 20.8, 12 aligned 31.2 / 35.4, 6 in two sextets 32.9 / 28.2; complex128 n = 9 (9) 64 shifts
+// 25.6 / 23.1, n = 11 (81) 18 33.9 / 32.8, 36 37.6 / 41.6; n = 12 (243) one shift 35.8 / 21.2, 18 aligned 46.9 / 51.3, 18
+// in four sextets 56.3 / 51.3.
+static bool mana_families_fit(const ManaPlan &P, uint64_t a0, uint64_t a1) {
+  const int64_t n = (int64_t)(a1 - a0), six = (n + (int64_t)(a0 % 3) + 5) / 6;
+  const int64_t tiles = pow3c(P.nh) / mana_rows_per_tile(MANA_NT, pow3c(P.nl - 2), true);  // per sextet
+  return P.families && six * tiles >= (P.dbl ? 512 : 256) && 20 * n >= (P.dbl ? 17 : 14) * 6 * six;
+}
+
 template <typename T>
 static int mana_t(const ManaPlan &P, const void *psi, uint64_t a0, uint64_t a1, double *sums, double *out, void *ws,
                   hipStream_t st) {
@@ -1039,8 +1054,9 @@ static int mana_t(const ManaPlan &P, const void *psi, uint64_t a0, uint64_t a1, 
   char *exch0 = w + accb * (1 + P.lanes);
   // With families, pairs are counted from the first multiple of 3 at or below a0, three to a sextet of
   // shifts (two families of three); shifts outside [a0, a1) are zero.
-  const uint64_t a_base = P.families ? a0 - a0 % 3 : a0;
-  const int64_t n_pairs = P.families ? 3 * (int64_t)((a1 - a_base + 5) / 6) : (int64_t)((a1 - a0 + 1) / 2);
+  const bool families = mana_families_fit(P, a0, a1);
+  const uint64_t a_base = families ? a0 - a0 % 3 : a0;
+  const int64_t n_pairs = families ? 3 * (int64_t)((a1 - a_base + 5) / 6) : (int64_t)((a1 - a0 + 1) / 2);
   const int64_t n_batches = (n_pairs + P.batch_pairs - 1) / P.batch_pairs;
   const int L = (P.lanes > 1 && n_batches > 1) ? 2 : 1;
   hipStream_t lst[2] = {st, st};
@@ -1063,7 +1079,7 @@ static int mana_t(const ManaPlan &P, const void *psi, uint64_t a0, uint64_t a1, 
     const int64_t p0 = k * P.batch_pairs;
     const int64_t nb = (n_pairs - p0) < P.batch_pairs ? (n_pairs - p0) : P.batch_pairs;
     void *ex_l = exch0 + (size_t)l * xb;
-    if (P.families) {
+    if (families) {
       ManaFamilyArgs A{};
       A.psi = psi;
       A.psi_bytes = (uint32_t)((size_t)pow3c(P.N) * sizeof(vec2<T>));

@@ -34,3 +34,18 @@ def test_few_shifts_run_beside_each_other(c64, n):
     print(f"[short ranges] n={n} c64={c64}", flush=True)
     ms = [profiled(hm, lambda: hm.sre_partial(x, (2.0,), 1000, 1000 + c), 50)["sre_rowpass_write"][1] for c in (1, count)]
     assert ms[1] < 1.6 * ms[0], ms
+
+
+@pytest.mark.parametrize("c64,n", [(True, 12), (False, 12)])
+def test_one_shift_of_mana_is_one_pair(c64, n):
+    """One shift takes less than the six of a sextet (padded to three pairs it took the same)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2601_07824_amd as hm
+    x = torch.from_numpy(S.gaussian_state(n, d=3, seed=8320)).to(torch.complex64 if c64 else torch.complex128).cuda()
+    print(f"[short ranges] mana n={n} c64={c64}", flush=True)
+    ms = []
+    for count in (1, 6):
+        t = profiled(hm, lambda: hm.mana_partial(x, 30, 30 + count), 50)
+        ms.append(t["mana_rowpass_write"][1] + t["mana_colpass"][1])
+    assert ms[0] < 0.85 * ms[1], ms
