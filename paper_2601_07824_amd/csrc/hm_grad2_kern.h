@@ -554,7 +554,7 @@ int grad2_t(const SrePlan &p, const void *psi, double q, double *out, void *grad
     A.exch = exch;
     A.nacc = nacc;
     A.qa = qa;
-    int e = launch_rows<T>(p.row_rb, p.nl, A, p.split != 0, st);
+    int e = launch_rows<T>(p.row_rb, p.nl, A, p.split != 0, p.group_split != 0, st);
     if (e) return e;
     ColPassArgs C{};
     C.exch = exch;

@@ -50,7 +50,8 @@ struct SrePlan {
   int row_rb;   // register-tile bits of the two-pass row pass
   int col_rb;   // register-tile bits of the column pass
   int pipe;     // 1: row pass of batch k and column pass of batch k-1 share one launch
-  int split;    // 1: pipelined tiles stage one component at a time through LDS (half the LDS)
+  int split;    // 1: tiles stage one component at a time through LDS (half the LDS)
+  int group_split;  // the same for the row pass by groups of shifts
   int streams;  // 2: sequential batches alternate between the caller's stream and an internal one
 };
 

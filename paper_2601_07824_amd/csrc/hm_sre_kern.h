@@ -713,7 +713,7 @@ constexpr int64_t row_group_min(int NL) { return NL == 10 ? 512 : 192; }
 // FP64 values (FP32 tiles of 2^4 values per thread, the gradient's: 2^7..2^10); the shifts below one group, among
 // them a = 0, run one by one.  Returns false where it does not apply (fewer rows per shift than a tile holds) or
 // the range is too short.
-template <typename T, int RB, int NL, int NT>
+template <typename T, int RB, int NL, int NT, bool SPLIT>
 static bool launch_rowgroup_nl(const RowPassArgs &A, int64_t skip, hipStream_t st) {
   constexpr int LG = ilog2c(NT) + RB - NL, GB = row_group_bits<T>(NL, RB);
   if (A.nh < LG) return false;
@@ -727,12 +727,12 @@ static bool launch_rowgroup_nl(const RowPassArgs &A, int64_t skip, hipStream_t s
   B.exch = (vec2<T> *)A.exch + (skip << A.nf);
   const int64_t groups = (int64_t)(((B.a0 + (uint64_t)B.n_slots - 1) >> GB) - (B.a0 >> GB) + 1);
   ProfScope prof("sre_rowpass_write", st);
-  hipLaunchKernelGGL((k_sre_rowgroup<T, NT, RB, NL, true>), dim3((unsigned)(groups << (A.nh - LG))), dim3(NT), 0, st, B);
+  hipLaunchKernelGGL((k_sre_rowgroup<T, NT, RB, NL, SPLIT>), dim3((unsigned)(groups << (A.nh - LG))), dim3(NT), 0, st, B);
   return true;
 }
-template <typename T>
+template <typename T, bool SPLIT>
 static bool launch_rowgroup(int rb, int NL, const RowPassArgs &A, int64_t skip, hipStream_t st) {
-#define HM_RG(RB, nl, nt)   case nl: return launch_rowgroup_nl<T, RB, nl, nt>(A, skip, st);
+#define HM_RG(RB, nl, nt)   case nl: return launch_rowgroup_nl<T, RB, nl, nt, SPLIT>(A, skip, st);
   if constexpr (sizeof(T) == 4) {
     if (rb == 5) switch (NL) {
         HM_RG(5, 8, 128) HM_RG(5, 9, 128) HM_RG(5, 10, 128) HM_RG(5, 11, 128) HM_RG(5, 12, 128) HM_RG(5, 13, 256)
@@ -749,11 +749,12 @@ static bool launch_rowgroup(int rb, int NL, const RowPassArgs &A, int64_t skip, 
   return false;
 }
 template <typename T>
-static int launch_rows(int rb, int NL, RowPassArgs A, bool split, hipStream_t st) {
+static int launch_rows(int rb, int NL, RowPassArgs A, bool split, bool group_split, hipStream_t st) {
   if (!A.rows && NL >= 7) {
     const uint64_t first = 1ull << row_group_bits<T>(NL, rb);
     int64_t skip = A.a0 < first ? (int64_t)(first - A.a0) : 0;
-    if (skip < A.n_slots && launch_rowgroup<T>(rb, NL, A, skip, st)) {
+    if (skip < A.n_slots && (group_split ? launch_rowgroup<T, true>(rb, NL, A, skip, st)
+                                         : launch_rowgroup<T, false>(rb, NL, A, skip, st))) {
       if (skip == 0) return OK;
       A.n_slots = skip;  // the rest is per shift
     }
@@ -887,7 +888,7 @@ int shift_sums_t(const SrePlan &p, const void *psi, const QArgs &qa, uint64_t a0
     A.exch = ln.exch;
     A.nacc = nacc;
     A.qa = qa;
-    int e = launch_rows<T>(p.row_rb, p.nl, A, p.split != 0, ln.st);
+    int e = launch_rows<T>(p.row_rb, p.nl, A, p.split != 0, p.group_split != 0, ln.st);
     if (e) return e;
     ColPassArgs C{};
     C.exch = ln.exch;
