@@ -961,10 +961,14 @@ static int launch_mana_families_nl(ManaFamilyArgs A, int nh, hipStream_t st) {
 template <typename T>
 static int launch_mana_families(int NL, int nh, ManaFamilyArgs A, hipStream_t st) {
   switch (NL) {
-    case 4: return launch_mana_families_nl<T, 4>(A, nh, st);
+    case 4:  // complex128 only
+      if constexpr (sizeof(T) == 8) return launch_mana_families_nl<T, 4>(A, nh, st);
+      break;
     case 5: return launch_mana_families_nl<T, 5>(A, nh, st);
     case 6: return launch_mana_families_nl<T, 6>(A, nh, st);
-    case 7: return launch_mana_families_nl<T, 7>(A, nh, st);
+    case 7:  // complex64 only
+      if constexpr (sizeof(T) == 4) return launch_mana_families_nl<T, 7>(A, nh, st);
+      break;
     default: break;
   }
   return fail(E_UNSUPPORTED, "mana: no family row-pass kernel for rows of 3^%d", NL);
