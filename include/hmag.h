@@ -88,7 +88,8 @@ const char *hm_version(void);
  *     after the other (half the LDS per workgroup, so more workgroups per CU): two-pass kernels
  *     with the default column register tiles, and workgroup-resident tiles of 2^10..2^14 (HM_C64)
  *     or 2^10..2^13 (HM_C128) values, which then also keep to a register budget of three or four
- *     waves per SIMD; the default for the resident tiles and for HM_C64 two-pass kernels.
+ *     waves per SIMD; the default for the resident tiles, for HM_C64 two-pass kernels and for the
+ *     two-pass row pass by groups of consecutive shifts.
  *   HM_OPT_STREAMS: sequential two-pass launches on 1 stream (the caller's) or 2 (batches alternate
  *     between the caller's stream and an internal stream of the library, forked from and joined
  *     back into the caller's stream with events, so results stay stream-ordered; twice the

@@ -827,10 +827,10 @@ struct ManaPlan {
   int lanes;  // two-pass batches alternate over this many streams (own exchange and accumulators)
 };
 
-// Two-pass default: one lane.  Two lanes let the VALU-bound row pass of one batch overlap the
-// memory-bound column pass of the other, but measured no faster at n = 12 (645 ms with 44-shift
-// batches against 641 ms on one stream; 713 ms with two 192 MiB exchanges, which no longer fit the
-// memory-side cache together).
+// Two-pass default: one lane.  Two lanes let one batch's row pass overlap the other's column pass: with half-size
+// batches (48 shifts) 436 ms against 468 at n = 12 in complex64, but 120 ms against 100 at n = 11 in complex128, and
+// with two 192 MiB exchanges, which do not fit the memory-side cache together, 546 and 116 ms.  hm_autotune_mana
+// measures both on the state at hand.
 static constexpr int MANA_STREAMS_DEFAULT = 1;
 
 // batch: X-shifts per two-pass launch pair (0 = 192 MiB of exchange); streams: 0 (default), 1, 2.
@@ -860,8 +860,8 @@ static int mana_plan(int N, int dbl, int64_t batch, int streams, ManaPlan *p) {
     P.nl = nl;
     P.nh = nh;
     const size_t per_pair = (size_t)pow3c(N) * (dbl ? 16 : 8);
-    // Untuned: 192 MiB of exchange per launch pair, inside the 256 MiB memory-side cache (at n = 12
-    // on MI355X: 0.66 s against 0.68 s at 256 MiB and 0.77-0.79 s at 512 MiB - 1 GiB).
+    // Untuned: 192 MiB of exchange per launch pair, inside the 256 MiB memory-side cache (at n = 12 in complex64
+    // 468 ms; 122 MiB 505 ms, 243 MiB 492 ms, 535 MiB 588 ms, 1.05 GiB 554 ms).
     int64_t b = batch > 0 ? (batch + 1) / 2 : (int64_t)((192ull << 20) / per_pair);
     if ((size_t)b * per_pair > (3ull << 30)) b = (int64_t)((3ull << 30) / per_pair);  // 32-bit offsets
     if (b < 1) b = 1;

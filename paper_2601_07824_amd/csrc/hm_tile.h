@@ -334,7 +334,8 @@ __device__ __forceinline__ T sum_kind(T (&re)[R], T (&im)[R], QKind kind, double
     default:
       if constexpr (POW) {
         // FP64: no branch around pow, so that the two chains of a pass step overlap (8 indices, N = 14:
-        // 40.4 -> 13.0 ms; N = 8 134 -> 122 us); FP32 keeps it (33.1 against 35.3 ms at N = 15).
+        // 40.4 -> 13.0 ms; N = 8 134 -> 122 us); FP32 keeps it (25.0 against 26.9 ms at N = 15, 187 against
+        // 192 us at N = 8).
         constexpr int C = sizeof(T) == 4 ? 8 : 4;
         each_real_rotating<T, R, (R < C ? R : C), 1>(re, im, [&](T x) {
           const T t = x * x;
