@@ -128,7 +128,10 @@ hm_status hm_set_option(hm_handle h, hm_option opt, int64_t value);
  * applies, and two-pass plans over exchange batches of 64/128/256 MiB, both LDS stagings,
  * sequential launches (one or two streams) with the default, 11, 12 or 13 row bits (and 14, 15 for
  * HM_C64 from n = 20 on), and pipelined
- * launches.  Options already set on the handle are kept fixed.  The fastest plan is stored in the handle; later calls
+ * launches; where a two-pass plan is the fastest, all of them again on a list of shifts (a quarter of
+ * the sample, at least 256).  Options already set on the handle are kept fixed.  The fastest plan is
+ * stored in the handle, one for ranges and one for lists of shifts (hm_sre_rows, hm_sre_sampled,
+ * hm_sre_mc); later calls
  * on the handle for the same (n, dtype) fill every option left automatic from it.  Candidates
  * whose workspace exceeds ws_bytes are skipped (hm_autotune_workspace gives the size that admits
  * all of them).  Blocks until the timings are done (it synchronises on events on `stream`).
@@ -155,7 +158,7 @@ hm_status hm_autotune_grad(hm_handle h, const void *psi, int n, hm_dtype dtype, 
                            void *ws, size_t ws_bytes, hipStream_t stream);
 hm_status hm_autotune_batched(hm_handle h, const void *const *psis, const int *ns, int batch, hm_dtype dtype,
                               double *out, void *ws, size_t ws_bytes, hipStream_t stream);
-/* The stored plan for (n, dtype): opts[0..7] = {HM_OPT_FORCE_PATH, HM_OPT_BATCH_SHIFTS,
+/* The stored plan for ranges of shifts of (n, dtype): opts[0..7] = {HM_OPT_FORCE_PATH, HM_OPT_BATCH_SHIFTS,
  * HM_OPT_ROW_RB, HM_OPT_COL_RB, HM_OPT_ROW_BITS, HM_OPT_PIPELINE, HM_OPT_LDS_SPLIT, HM_OPT_STREAMS}
  * values (host array of 8), and its measured milliseconds per X-shift.  HM_E_ARG if none is
  * stored. */

@@ -223,7 +223,7 @@ hm_status hm_workspace_size(hm_handle h, hm_op op, int n, hm_dtype dtype, int n_
       if (n_q < 1 || n_q > HM_MAX_Q) return (hm_status)fail(E_ARG, "n_q = %d outside [1, %d]", n_q, HM_MAX_Q);
       if (count < 0) return (hm_status)fail(E_ARG, "count = %lld < 0", (long long)count);
       SrePlan p;
-      HM_TRY(sre_plan(n, dbl, plan_opts(h, n, dbl), &p));
+      HM_TRY(sre_plan(n, dbl, plan_opts(h, n, dbl, true), &p));
       *bytes = sre_workspace(p, n_q, 0);
       return HM_OK;
     }
@@ -243,7 +243,7 @@ hm_status hm_workspace_size(hm_handle h, hm_op op, int n, hm_dtype dtype, int n_
     case HM_OP_SRE_SAMPLED: {
       if (count < 2) return (hm_status)fail(E_ARG, "sampled: count = %lld < 2", (long long)count);
       SrePlan p;
-      HM_TRY(sre_plan(n, dbl, plan_opts(h, n, dbl), &p));
+      HM_TRY(sre_plan(n, dbl, plan_opts(h, n, dbl, true), &p));
       *bytes = align256((size_t)(count + 1) * 2 * sizeof(double)) + sre_workspace(p, 1, 0);
       return HM_OK;
     }
@@ -324,7 +324,7 @@ hm_status hm_sre_rows(hm_handle h, const void *psi, int n, hm_dtype dtype, const
   QArgs qa;
   HM_TRY(check_q(q, n_q, &qa));
   SrePlan p;
-  HM_TRY(sre_plan(n, dtype == HM_C128, plan_opts(h, n, dtype == HM_C128), &p));
+  HM_TRY(sre_plan(n, dtype == HM_C128, plan_opts(h, n, dtype == HM_C128, true), &p));
   if (n_rows == 0) return HM_OK;
   HM_TRY(check_ptr(rows, 8, "rows"));
   HM_TRY(check_ptr(row_sums, 8, "row_sums"));
@@ -594,7 +594,7 @@ hm_status hm_sre_sampled(hm_handle h, const void *psi, int n, hm_dtype dtype, co
   const double q2 = 2.0;
   HM_TRY(check_q(&q2, 1, &qa));
   SrePlan p;
-  HM_TRY(sre_plan(n, dtype == HM_C128, plan_opts(h, n, dtype == HM_C128), &p));
+  HM_TRY(sre_plan(n, dtype == HM_C128, plan_opts(h, n, dtype == HM_C128, true), &p));
   const size_t rs_bytes = align256((size_t)(n_rows + 1) * 2 * sizeof(double));
   HM_TRY(check_ws(ws, ws_bytes, rs_bytes + sre_workspace(p, 1, 0)));
   HM_TRY(norm_ok(h, psi, 2, n, dtype, stream));
@@ -611,7 +611,7 @@ hm_status hm_sre_mc_workspace(hm_handle h, int n, hm_dtype dtype, const hm_mc_pa
   HM_TRY(check_dtype(dtype));
   HM_TRY(mc_check(n, params));
   SrePlan p;
-  HM_TRY(sre_plan(n, dtype == HM_C128, plan_opts(h, n, dtype == HM_C128), &p));
+  HM_TRY(sre_plan(n, dtype == HM_C128, plan_opts(h, n, dtype == HM_C128, true), &p));
   return (hm_status)mc_workspace(p, params, bytes);
 }
 
@@ -629,7 +629,7 @@ hm_status hm_sre_mc(hm_handle h, const void *psi, int n, hm_dtype dtype, const h
   HM_TRY(check_ptr(out, 8, "out"));
   HM_TRY(check_ptr(trace, 8, "trace"));
   SrePlan p;
-  HM_TRY(sre_plan(n, dtype == HM_C128, plan_opts(h, n, dtype == HM_C128), &p));
+  HM_TRY(sre_plan(n, dtype == HM_C128, plan_opts(h, n, dtype == HM_C128, true), &p));
   size_t need = 0;
   HM_TRY(mc_workspace(p, params, &need));
   HM_TRY(check_ws(ws, ws_bytes, need));
@@ -736,7 +736,7 @@ hm_status hm_tune_query(hm_handle h, int n, hm_dtype dtype, int64_t *opts, doubl
   if (!h || !opts) return (hm_status)fail(E_ARG, "h or opts is NULL");
   HM_TRY(check_dtype(dtype));
   for (const auto &t : h->tuned)
-    if (t.n == n && t.dbl == (dtype == HM_C128)) {
+    if (t.n == n && t.dbl == (dtype == HM_C128) && !t.rows) {
       const PlanOpts &o = t.opts;
       const int64_t v[8] = {o.force_path, o.batch, o.row_rb, o.col_rb, o.row_bits, o.pipeline, o.lds_split, o.streams};
       for (int i = 0; i < 8; ++i) opts[i] = v[i];

@@ -100,10 +100,11 @@ struct PlanOpts {
   int batch_launch = 0;  // hm_sre_batched: 0 automatic, 1 one persistent launch, 2 one launch per size class
 };
 
-// Plan options chosen by the autotuner for one (qubit count, dtype).
+// Plan options chosen by the autotuner for one (qubit count, dtype): for ranges of shifts, or for lists.
 struct TunedPlan {
   int n;
   int dbl;
+  int rows;  // 1: lists of shifts
   PlanOpts opts;
   double ms_per_shift;
 };
@@ -144,7 +145,7 @@ size_t sre_autotune_workspace(const hm_context *h, int n, int dbl, int64_t sampl
 
 // Options for planning (n, dbl) on handle h: every field the caller left automatic (0) is taken
 // from the autotuner's entry for (n, dbl), if there is one.
-PlanOpts plan_opts(const hm_context *h, int n, int dbl);
+PlanOpts plan_opts(const hm_context *h, int n, int dbl, bool rows = false);
 // The same for mana (X-shifts per launch pair, streams) and the gradient (path).
 void mana_opts(const hm_context *h, int n, int dbl, int64_t *batch, int *streams);
 PlanOpts grad_opts(const hm_context *h, int n, int dbl);

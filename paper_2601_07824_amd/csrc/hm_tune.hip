@@ -18,10 +18,12 @@
 
 namespace hm {
 
-PlanOpts plan_opts(const hm_context *h, int n, int dbl) {
+PlanOpts plan_opts(const hm_context *h, int n, int dbl, bool rows) {
   PlanOpts o = h->opts;
+  bool list = false;  // lists of shifts go by the range's entry where they have none of their own
+  for (const auto &t : h->tuned) list |= rows && t.rows && t.n == n && t.dbl == dbl;
   for (const auto &t : h->tuned) {
-    if (t.n != n || t.dbl != dbl) continue;
+    if (t.n != n || t.dbl != dbl || (t.rows != 0) != list) continue;
     if (!o.force_path) o.force_path = t.opts.force_path;
     if (!o.batch) o.batch = t.opts.batch;
     if (!o.row_rb) o.row_rb = t.opts.row_rb;
@@ -236,66 +238,78 @@ static int64_t tune_shifts(int n, int64_t sample) {
   return sample < all ? sample : all;
 }
 
+// Lists are timed over the shifts of the sample's size too, a quarter of a long one.
+static int64_t tune_rows(int64_t k) { return k / 4 > 256 ? k / 4 : k < 256 ? k : 256; }
+
+// Distinct-looking shifts in [1, 2^n) (splitmix64 of the index).
+__global__ void k_tune_rows(uint64_t *rows, int64_t k, int n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= k) return;
+  uint64_t z = ((uint64_t)i + 1u) * 0x9E3779B97F4A7C15ull;
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+  z = (z ^ (z >> 31)) & ((1ull << n) - 1ull);
+  rows[i] = z ? z : 1u;
+}
+
 size_t sre_autotune_workspace(const hm_context *h, int n, int dbl, int64_t sample) {
   const int64_t k = tune_shifts(n, sample);
-  size_t need = 256;
+  size_t need = 256, list = 0;
   for (const auto &o : candidates(h, n, dbl)) {
     SrePlan p;
     if (sre_plan(n, dbl, o, &p) != OK) continue;
     const size_t b = sre_workspace(p, 1, k);
     if (b > need) need = b;
+    if (p.path == 2) list = align256((size_t)tune_rows(k) * sizeof(uint64_t));
   }
-  return need;
+  return need + list;
+}
+
+// The fastest candidate over k shifts: [0, k), or the list rows.  Returns OK with best->ms_per_shift < 0 if no
+// candidate fits ws_bytes.
+static int tune_pick(hm_context *h, const void *psi, int n, int dbl, const uint64_t *rows, int64_t k, void *ws,
+                     size_t ws_bytes, hipStream_t st, TunedPlan *best) {
+  QArgs qa{};
+  qa.nq = 1;
+  qa.q[0] = 2.0;
+  *best = TunedPlan{};
+  best->ms_per_shift = -1.0;
+  for (const auto &o : candidates(h, n, dbl)) {
+    SrePlan p;
+    if (sre_plan(n, dbl, o, &p) != OK) continue;
+    if (sre_workspace(p, 1, k) > ws_bytes) continue;
+    float ms = 0.f;
+    const int err = time_once(st, [&]() { return sre_run(p, psi, qa, 0, rows, k, nullptr, nullptr, nullptr, ws, st); }, &ms);
+    if (err) return err;
+    const double per = (double)ms / (double)k;
+    if (best->ms_per_shift < 0 || per < best->ms_per_shift) *best = TunedPlan{n, dbl, rows != nullptr, o, per};
+  }
+  return OK;
 }
 
 int sre_autotune(hm_context *h, const void *psi, int n, int dbl, int64_t sample, void *ws, size_t ws_bytes,
                  hipStream_t st, TunedPlan *best_out) {
   const int64_t k = tune_shifts(n, sample);
-  QArgs qa{};
-  qa.nq = 1;
-  qa.q[0] = 2.0;
-  hipEvent_t e0, e1;
-  if (hipEventCreate(&e0) != hipSuccess) return fail(E_HIP, "autotune: hipEventCreate failed");
-  if (hipEventCreate(&e1) != hipSuccess) {
-    (void)hipEventDestroy(e0);
-    return fail(E_HIP, "autotune: hipEventCreate failed");
-  }
-  TunedPlan best{};
-  best.ms_per_shift = -1.0;
-  int err = OK, tried = 0;
-  for (const auto &o : candidates(h, n, dbl)) {
-    SrePlan p;
-    if (sre_plan(n, dbl, o, &p) != OK) continue;
-    if (sre_workspace(p, 1, k) > ws_bytes) continue;
-    // warm-up run, then one timed run over the same k shifts
-    if ((err = sre_run(p, psi, qa, 0, nullptr, k, nullptr, nullptr, nullptr, ws, st)) != OK) break;
-    if (hipEventRecord(e0, st) != hipSuccess) { err = fail(E_HIP, "autotune: hipEventRecord failed"); break; }
-    if ((err = sre_run(p, psi, qa, 0, nullptr, k, nullptr, nullptr, nullptr, ws, st)) != OK) break;
-    if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
-      err = fail(E_HIP, "autotune: %s", hipGetErrorString(hipGetLastError()));
-      break;
-    }
-    float ms = 0.f;
-    (void)hipEventElapsedTime(&ms, e0, e1);
-    const double per = (double)ms / (double)k;
-    ++tried;
-    if (best.ms_per_shift < 0 || per < best.ms_per_shift) {
-      best.n = n;
-      best.dbl = dbl;
-      best.opts = o;
-      best.ms_per_shift = per;
-    }
-  }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
+  TunedPlan best, list;
+  list.ms_per_shift = -1.0;
+  int err = tune_pick(h, psi, n, dbl, nullptr, k, ws, ws_bytes, st, &best);
   if (err) return err;
-  if (!tried) return fail(E_WORKSPACE, "autotune: no candidate plan fits a workspace of %zu bytes", ws_bytes);
-  for (auto it = h->tuned.begin(); it != h->tuned.end(); ++it)
-    if (it->n == n && it->dbl == dbl) {
-      h->tuned.erase(it);
-      break;
-    }
+  if (best.ms_per_shift < 0)
+    return fail(E_WORKSPACE, "autotune: no candidate plan fits a workspace of %zu bytes", ws_bytes);
+  // Two-pass ranges go by groups of shifts, lists shift by shift, so their best plans differ (complex64 n = 24, 512
+  // rows: 22.0 ms with the range's plan, 21.0 with one launch a shift on two streams).
+  const int64_t kr = tune_rows(k);
+  const size_t rb = align256((size_t)kr * sizeof(uint64_t));
+  SrePlan p;
+  if (sre_plan(n, dbl, best.opts, &p) == OK && p.path == 2 && ws_bytes > rb) {
+    hipLaunchKernelGGL(k_tune_rows, dim3((unsigned)((kr + 255) / 256)), dim3(256), 0, st, (uint64_t *)ws, kr, n);
+    err = tune_pick(h, psi, n, dbl, (const uint64_t *)ws, kr, (char *)ws + rb, ws_bytes - rb, st, &list);
+    if (err) return err;
+  }
+  for (size_t i = h->tuned.size(); i-- > 0;)
+    if (h->tuned[i].n == n && h->tuned[i].dbl == dbl) h->tuned.erase(h->tuned.begin() + (long)i);
   h->tuned.push_back(best);
+  if (list.ms_per_shift >= 0) h->tuned.push_back(list);
   if (best_out) *best_out = best;
   return OK;
 }
